@@ -1214,6 +1214,37 @@ __global__ void k_probe_extract(const float* buf, int32_t B, int64_t T, int32_t 
   out[_i] = buf[(t * probe_rows + off + j) * B + b];
 }
 
+// The same for B >= kExtractB, as a transposition through LDS: the output is
+// [B][q] with q = t w + j, so a workgroup takes 64 values of q and 64 batch
+// columns, reads each q as a row segment along B and writes each column as a
+// segment along q.  Bound by the copy (one read, one write of the record); one
+// thread per output element reads B floats apart instead, a cache line for
+// each value: a record of 1024 values, 256 columns and 50 steps takes 65 us,
+// here 39 us.
+// Below kExtractB columns a line still serves several lanes of the simple form
+// and a 64-wide tile would be mostly empty.  Grid (ceil(T w / 64), ceil(B / 64)).
+constexpr int kExtractB = 16;
+
+__global__ void __launch_bounds__(256) k_probe_extract_t(const float* buf, int32_t B, int64_t T, int32_t probe_rows,
+                                                         int32_t off, int32_t w, float* out) {
+  __shared__ float tile[64][65];
+  const int64_t Q = T * w, q0 = (int64_t)blockIdx.x * 64, t0 = q0 / w;
+  const int32_t j0 = (int32_t)(q0 - t0 * w);
+  const int32_t b0 = blockIdx.y * 64, lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+  const bool inb = b0 + lane < B;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int32_t r = wave + 4 * i, j = j0 + r, dt = j / w;
+    if (inb && q0 + r < Q) tile[r][lane] = buf[((t0 + dt) * probe_rows + off + (j - dt * w)) * B + b0 + lane];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int32_t b = wave + 4 * i;
+    if (b0 + b < B && q0 + lane < Q) out[(int64_t)(b0 + b) * Q + q0 + lane] = tile[lane][b];
+  }
+}
+
 // A bit-recorded spike probe read out as values: out[b][t][i] (the layout of
 // every probe read) is `mag` (amplitude / dt) where bit i of step t, column b
 // is set, else 0.  The probe's words start at word row `off` of `words` per step.

@@ -1690,6 +1690,20 @@ ms_status ms_sim_probe_width(const ms_sim* s, int32_t probe, int32_t* w) {
   });
 }
 
+// Probe `probe`'s float record so far into out [B][T][w] (device memory).
+static void extract_probe(ms_sim* s, int32_t probe, float* out) {
+  const Plan& p = *s->plan;
+  const int32_t w = p.probe_width[probe];
+  const int64_t T = s->steps_total, n = (int64_t)s->B * T * w;
+  if (s->B >= kExtractB && s->B <= 64 * 65535 && T * w <= 64LL * 2147483647)   // within the grid's limits
+    hipLaunchKernelGGL(k_probe_extract_t, dim3((unsigned)((T * w + 63) / 64), (unsigned)((s->B + 63) / 64)), dim3(256),
+                       0, s->stream, (const float*)s->probe_buf, s->B, T, s->probe_rows, p.probe_row_offset[probe], w,
+                       out);
+  else
+    hipLaunchKernelGGL(k_probe_extract, dim3(grid_for(n)), dim3(kBlock), 0, s->stream, (const float*)s->probe_buf,
+                       s->B, T, s->probe_rows, p.probe_row_offset[probe], w, out);
+}
+
 ms_status ms_sim_probe_read(ms_sim* s, int32_t probe, float* out, int64_t cap, int32_t out_on_device) {
   return guarded([&] {
     if (!s || !out) fail(MS_E_INVALID, "NULL argument");
@@ -1707,8 +1721,7 @@ ms_status ms_sim_probe_read(ms_sim* s, int32_t probe, float* out, int64_t cap, i
                          (const uint32_t*)s->bits_buf, s->B, T, s->bit_words, s->bit_off[probe], w,
                          s->spike_mag[probe], tmp);
     else
-      hipLaunchKernelGGL(k_probe_extract, dim3(grid_for(n)), dim3(kBlock), 0, s->stream,
-                         (const float*)s->probe_buf, s->B, T, s->probe_rows, p.probe_row_offset[probe], w, tmp);
+      extract_probe(s, probe, tmp);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && !out_on_device)
       e = hipMemcpyAsync(out, tmp, (size_t)n * 4, hipMemcpyDeviceToHost, s->stream);
@@ -1738,8 +1751,7 @@ ms_status ms_sim_probe_read_static(ms_sim* s, int32_t probe, float* out, int64_t
                          (const uint32_t*)s->bits_buf, s->B, T, s->bit_words, s->bit_off[probe], w,
                          s->spike_mag[probe], stage);
     else
-      hipLaunchKernelGGL(k_probe_extract, dim3(grid_for(n)), dim3(kBlock), 0, s->stream,
-                         (const float*)s->probe_buf, s->B, T, s->probe_rows, p.probe_row_offset[probe], w, stage);
+      extract_probe(s, probe, stage);
     HIPCHECK(hipGetLastError());
     HIPCHECK(hipMemcpyAsync(out, stage, (size_t)n * 4, hipMemcpyDeviceToHost, s->stream));
     HIPCHECK(hipStreamSynchronize(s->stream));
