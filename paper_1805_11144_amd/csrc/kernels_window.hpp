@@ -782,67 +782,159 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(CHAIN 
 // ------------------------------------------------- products on fp32 MFMA
 // dst[m][c] += sum_k W[m][k] x[k][c] for every op of a merged DotInc group and
 // every (step, column) c of the window: per op a dense M x K by K x (T*B)
-// product.  Workgroup tile 64 x 64 (M x columns), K in slices of 16 staged in
-// LDS; each of the four wavefronts owns a 32 x 32 quarter and accumulates it
-// with v_mfma_f32_32x32x2f32 (A lane l: row l%32, k l/32; B lane l: k l/32,
-// column l%32; result register v: row 8(v/4) + 4(l/32) + v%4, column l%32).
+// product on v_mfma_f32_32x32x2f32 (A lane l: row l%32, k l/32; B lane l: k
+// l/32, column l%32; result register v: row 8(v/4) + 4(l/32) + v%4, column
+// l%32).  Every tile shape below adds k in order, two at a time, into one
+// accumulator per element, so the shapes give the same bits.
 typedef float mfma_f16x __attribute__((ext_vector_type(16)));
+typedef float gemm_f4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGemmBM = 64, kGemmBN = 64, kGemmBK = 16;
+// W is read from a packed copy made by k_w_pack: per op and row tile of 64 the
+// [k][64 rows] transpose, rows past M and k past K (up to a multiple of
+// kGemmPadK) zero.  A slice is then whole 16-byte words in the layout that LDS
+// keeps (the row-major W took 8 scalar LDS stores per thread and slice, and its
+// edges bounds tests), and a lane's fragments are at fixed offsets.
+constexpr int kGemmPadK = 32;
 
-// One 64 x 64 tile (rows m0.., columns c0.. of the window) of op's product,
-// by a workgroup of 256 threads, staging through As and Bs.
-__device__ __forceinline__ void gemm64_tile(const WView& w, int32_t M, int32_t K, const float* Wt,
-                                            const int32_t* w_row, const int32_t* x_row, const int32_t* d_row,
-                                            int xblk, int op, int64_t m0, int64_t c0,
-                                            float (*As)[kGemmBM + 4], float (*Bs)[kGemmBN + 4]) {
+// Floats of one op's packed weights.
+__host__ __device__ __forceinline__ int64_t packed_elems(int32_t M, int32_t K) {
+  return (int64_t)((M + 63) / 64) * 64 * (((int64_t)K + kGemmPadK - 1) / kGemmPadK * kGemmPadK);
+}
+
+// Workgroup per (op, row tile, kGemmPadK k); through LDS, so that reads and
+// writes are both coalesced.  tr: element (m, k) of an op is at row k, column m
+// of the [K][M] block at w_row[op] (the products that carry adjoints back
+// multiply by the transpose).
+__global__ void __launch_bounds__(256) k_w_pack(const float* W, const int32_t* w_row, int32_t M, int32_t K,
+                                                int32_t mtiles, int32_t ktiles, int tr, float* P) {
+  __shared__ float tile[kGemmPadK][65];
+  const int64_t blk = blockIdx.x;
+  const int32_t kt = (int32_t)(blk % ktiles), mt = (int32_t)(blk / ktiles % mtiles);
+  const int64_t r0 = G(w_row)[blk / ((int64_t)ktiles * mtiles)];
+  const int tid = threadIdx.x;
+#pragma unroll
+  for (int i = 0; i < kGemmPadK * 64 / 256; ++i) {
+    const int e = tid + 256 * i, mm = tr ? e % 64 : e / kGemmPadK, kk = tr ? e / 64 : e % kGemmPadK;
+    const int64_t m = (int64_t)mt * 64 + mm, k = (int64_t)kt * kGemmPadK + kk;
+    tile[kk][mm] = m < M && k < K ? (tr ? G(W)[(r0 + k) * M + m] : G(W)[(r0 + m) * K + k]) : 0.0f;
+  }
+  __syncthreads();
+  float* d = P + blk * (kGemmPadK * 64);
+#pragma unroll
+  for (int i = 0; i < kGemmPadK * 64 / 256; ++i) d[tid + 256 * i] = tile[(tid + 256 * i) / 64][tid % 64];
+}
+
+// One BM x BN tile (rows m0 .., columns c0 ..; 128 or 64) of a product by 256
+// threads, each wavefront a quarter; slices of KS k in two LDS buffers (As, Bs:
+// 2 KS (BM + 4) and 2 KS (BN + 4) floats).
+//
+// Bound by MFMA; what held the earlier form at half its rate was the loads of
+// the next slice, awaited after one slice of products.  Here a slice is in
+// registers one slice before it is stored to LDS and two before it is used,
+// and the store and the next fetch stand in the middle of a slice's products.
+// Measured on 1024 x 1024 by 1024 x 12288 (three tiles per CU): 264 -> 196 us
+// with the products stored, 98 -> 131 of 157 TFLOP/s.
+//
+// VEC: B % 4 == 0, so the rows of x are 16-byte aligned.  Columns past N are read
+// at the last whole word (column) instead and never stored; k past K is zeroed,
+// since what follows in memory may not be finite.
+template <int BM, int BN, int KS, bool VEC>
+__device__ __forceinline__ void gemm_tile(const WView& w, int32_t M, int32_t K, const float* P, const float* X,
+                                          float* C, int64_t m0, int64_t c0, int store, float* As, float* Bs) {
+  constexpr int LA = BM + 4, LB = BN + 4, MI = BM / 64, NI = BN / 64;
+  constexpr int QA = KS * BM / 1024, QB = KS * BN / 1024;     // float4 per thread and slice
+  constexpr int RA = 1024 / BM, RB = VEC ? 1024 / BN : 256 / BN;   // rows of a slice per pass of the workgroup
   const int64_t N = (int64_t)w.T * w.B;
   const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
   const int wm = wave / 2, wn = wave % 2;
-  gptr<float> A = G(Wt) + (int64_t)G(w_row)[op] * K;
-  const float* X = w.va + (int64_t)G(x_row)[op] * w.vs + (int64_t)xblk * w.B;
-  float* C = w.va + (int64_t)G(d_row)[op] * w.vs + w.B;
-  mfma_f16x acc;
+  const int ka = tid / (BM / 4), ma = 4 * (tid % (BM / 4));
+  const int kb = VEC ? tid / (BN / 4) : tid / BN, nb = VEC ? 4 * (tid % (BN / 4)) : tid % BN;
+  // rows past the last packed tile (128-row tiles of a product with an odd
+  // number of packed tiles) read the last one again and are never stored
+  const int32_t kp = (K + kGemmPadK - 1) / kGemmPadK * kGemmPadK, mtl = (M + 63) / 64 - 1;
+  const float* pa = P + (int64_t)min((int32_t)(m0 / 64) + ma / 64, mtl) * kp * 64 + (int64_t)ka * 64 + ma % 64;
+  const float* pb = X + (int64_t)kb * w.vs + min(c0 + nb, N - (VEC ? 4 : 1));
+  const int32_t ns = (K + KS - 1) / KS;
+  gemm_f4 ra[QA], rb[QB];
+  auto fetch = [&](int32_t s) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  for (int32_t k0 = 0; k0 < K; k0 += kGemmBK) {
+    for (int q = 0; q < QA; ++q)
+      ra[q] = *(const __attribute__((address_space(1))) gemm_f4*)(pa + ((int64_t)s * KS + RA * q) * 64);
+    const float* p = pb + (int64_t)s * KS * w.vs;
+    const bool whole = (s + 1) * KS <= K;
+    if constexpr (VEC) {
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int idx = tid + q * 256;
-      const int mm = idx / kGemmBK, kk = idx % kGemmBK;
-      const int64_t m = m0 + mm;
-      const int32_t k = k0 + kk;
-      As[kk][mm] = (m < M && k < K) ? A[m * K + k] : 0.0f;
-      const int kb = idx / kGemmBN, jj = idx % kGemmBN;
-      const int32_t kx = k0 + kb;
-      const int64_t c = c0 + jj;
-      Bs[kb][jj] = (kx < K && c < N) ? X[(int64_t)kx * w.vs + c] : 0.0f;
+      for (int q = 0; q < QB; ++q)
+        rb[q] = whole || s * KS + kb + RB * q < K ? *(const gemm_f4*)(p + (int64_t)RB * q * w.vs)
+                                                  : gemm_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4 * QB; ++q)
+        rb[q / 4][q % 4] = whole || s * KS + kb + RB * q < K ? p[(int64_t)RB * q * w.vs] : 0.0f;
     }
-    __syncthreads();
+  };
+  auto stash = [&](int buf) {
+    float* a = As + buf * KS * LA + ka * LA + ma;
+    float* b = Bs + buf * KS * LB + kb * LB + nb;
 #pragma unroll
-    for (int kk = 0; kk < kGemmBK; kk += 2) {
-      const float a = As[kk + lane / 32][wm * 32 + lane % 32];
-      const float b = Bs[kk + lane / 32][wn * 32 + lane % 32];
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+    for (int q = 0; q < QA; ++q) *(gemm_f4*)(a + RA * q * LA) = ra[q];
+    if constexpr (VEC) {
+#pragma unroll
+      for (int q = 0; q < QB; ++q) *(gemm_f4*)(b + RB * q * LB) = rb[q];
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4 * QB; ++q) b[RB * q * LB] = rb[q / 4][q % 4];
+    }
+  };
+  mfma_f16x acc[MI][NI];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+  fetch(0);
+  stash(0);
+  if (ns > 1) fetch(1);
+  __syncthreads();
+  for (int32_t s = 0; s < ns; ++s) {
+    const float* ap = As + ((s & 1) * KS + lane / 32) * LA + wm * (BM / 2) + lane % 32;
+    const float* bp = Bs + ((s & 1) * KS + lane / 32) * LB + wn * (BN / 2) + lane % 32;
+#pragma unroll
+    for (int h = 0; h < KS / 16; ++h) {
+      float a[8][MI], b[8][NI];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i) a[kk][i] = ap[(16 * h + 2 * kk) * LA + 32 * i];
+#pragma unroll
+        for (int j = 0; j < NI; ++j) b[kk][j] = bp[(16 * h + 2 * kk) * LB + 32 * j];
+      }
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        if (h == KS / 32 && kk == (KS % 32 ? 4 : 0)) {   // halfway: the registers hold slice s + 1
+          if (s + 1 < ns) stash((s + 1) & 1);
+          if (s + 2 < ns) fetch(s + 2);
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NI; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[kk][i], b[kk][j], acc[i][j], 0, 0, 0);
+      }
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int v = 0; v < 16; ++v) {
-    const int64_t m = m0 + wm * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
-    const int64_t c = c0 + wn * 32 + lane % 32;
-    if (m < M && c < N) C[m * w.vs + c] += acc[v];
-  }
-}
-
-__global__ void __launch_bounds__(256) k_w_gemm(WView w, int32_t M, int32_t K, int32_t mtiles, const float* Wt,
-                                                const int32_t* w_row, const int32_t* x_row, const int32_t* d_row,
-                                                int xblk) {
-  __shared__ float As[kGemmBK][kGemmBM + 4];
-  __shared__ float Bs[kGemmBK][kGemmBN + 4];
-  const int op = blockIdx.y / mtiles, mt = blockIdx.y - op * mtiles;
-  gemm64_tile(w, M, K, Wt, w_row, x_row, d_row, xblk, op, (int64_t)mt * kGemmBM, (int64_t)blockIdx.x * kGemmBN,
-              As, Bs);
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NI; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int64_t m = m0 + wm * (BM / 2) + i * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
+        const int64_t c = c0 + wn * (BN / 2) + j * 32 + lane % 32;
+        if (m < M && c < N) C[m * w.vs + c] = (store ? 0.0f : C[m * w.vs + c]) + acc[i][j][v];
+      }
 }
 
 // Products with few rows and a deep K (M <= 16, K >= 256): one lane per
@@ -932,136 +1024,45 @@ __device__ __forceinline__ TileIdx xcd_tile(uint32_t mtiles, uint32_t ntiles, ui
   return t;
 }
 
-// Larger products: workgroup tile 128 x 128, K in slices of 16, double-buffered
-// LDS; each of the four wavefronts owns a 64 x 64 quarter as 2 x 2 blocks of
-// v_mfma_f32_32x32x2f32.  The next slice is fetched into registers (four
-// float4 per thread) while the current one is multiplied.  Used when K and B
-// are multiples of 4 (so rows of W and of x are 16-byte aligned).
-constexpr int kG2M = 128, kG2N = 128, kG2K = 16;
+// The products of a merged DotInc group.  Workgroups 0 .. gbig - 1 take 128 x 128
+// tiles of the first ntiles column tiles, the others 64 x 64 tiles of the
+// columns after them: when the 128 x 128 tiles number a little more than a
+// whole multiple of the CUs, the last column tiles would leave most CUs idle
+// while a few finish one extra tile; as quarter-size tiles the CUs take them up
+// beside their large ones.  store: nothing has been added to the destination
+// yet (its reset was dropped), so the products are stored.
+template <bool VEC>
+__global__ void __launch_bounds__(256, 3) k_w_gemm2(WView w, int32_t M, int32_t K, int32_t mtiles, int32_t ntiles,
+                                                    int32_t nops, const float* P, const int32_t* x_row,
+                                                    const int32_t* d_row, int xblk, uint32_t gbig, int store) {
+  __shared__ __attribute__((aligned(16))) float As[2 * 16 * 132], Bs[2 * 16 * 132];
+  const int64_t N = (int64_t)w.T * w.B, cs = (int64_t)ntiles * 128;
+  const bool small = blockIdx.x >= gbig;
+  const TileIdx t = small ? xcd_tile((uint32_t)((M + 63) / 64), (uint32_t)((N - cs + 63) / 64), nops, blockIdx.x - gbig)
+                          : xcd_tile(mtiles, ntiles, nops, blockIdx.x);
+  if (!t.live) return;
+  const float* X = w.va + (int64_t)G(x_row)[t.op] * w.vs + (int64_t)xblk * w.B;
+  float* C = w.va + (int64_t)G(d_row)[t.op] * w.vs + w.B;
+  const int64_t m0 = (int64_t)t.mt * (small ? 64 : 128), c0 = small ? cs + (int64_t)t.nt * 64 : (int64_t)t.nt * 128;
+  const float* Pop = P + (int64_t)t.op * packed_elems(M, K);
+  if (small) gemm_tile<64, 64, 16, VEC>(w, M, K, Pop, X, C, m0, c0, store, As, Bs);
+  else gemm_tile<128, 128, 16, VEC>(w, M, K, Pop, X, C, m0, c0, store, As, Bs);
+}
 
-//
-// Tail split: when the 128 x 128 tiles number a little more than a whole
-// multiple of the CUs, the last column tiles would leave most CUs idle while
-// a few finish one extra tile.  The launch then covers only the first ntiles
-// column tiles with 128 x 128 tiles (workgroups 0 .. gbig-1) and the columns
-// after them with 64 x 64 tiles (workgroups gbig ..), a quarter of the work
-// each, which the CUs take up beside their large tiles.  Both tile sizes add
-// k in the same order (slices of 16, pairs on v_mfma_f32_32x32x2f32), so the
-// split does not change any result.
-__global__ void __launch_bounds__(256, 4) k_w_gemm2(WView w, int32_t M, int32_t K, int32_t mtiles, int32_t ntiles,
-                                                 int32_t nops, const float* Wt, const int32_t* w_row,
-                                                 const int32_t* x_row, const int32_t* d_row, int xblk,
-                                                 uint32_t gbig) {
-  typedef float f4v __attribute__((ext_vector_type(4)));
-  __shared__ float As[2][kG2K][kG2M + 4];
-  __shared__ float Bs[2][kG2K][kG2N + 4];
-  const int64_t N = (int64_t)w.T * w.B;
-  if (blockIdx.x >= gbig) {   // 64 x 64 tiles of the columns after the large tiles
-    const int64_t cs = (int64_t)ntiles * kG2N;
-    const uint32_t mt2 = (uint32_t)((M + kGemmBM - 1) / kGemmBM);
-    const uint32_t nt2 = (uint32_t)((N - cs + kGemmBN - 1) / kGemmBN);
-    const TileIdx st = xcd_tile(mt2, nt2, nops, blockIdx.x - gbig);
-    if (!st.live) return;
-    gemm64_tile(w, M, K, Wt, w_row, x_row, d_row, xblk, st.op, (int64_t)st.mt * kGemmBM,
-                cs + (int64_t)st.nt * kGemmBN, (float(*)[kGemmBM + 4]) & As[0][0][0],
-                (float(*)[kGemmBN + 4]) & Bs[0][0][0]);
-    return;
-  }
-  const TileIdx ti = xcd_tile(mtiles, ntiles, nops, blockIdx.x);
-  if (!ti.live) return;
-  const int op = ti.op, mt = ti.mt;
-  const int64_t m0 = (int64_t)mt * kG2M, c0 = (int64_t)ti.nt * kG2N;
-  const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-  const int wm = wave / 2, wn = wave % 2;
-  gptr<float> A = G(Wt) + (int64_t)G(w_row)[op] * K;
-  const float* X = w.va + (int64_t)G(x_row)[op] * w.vs + (int64_t)xblk * w.B;
-  float* C = w.va + (int64_t)G(d_row)[op] * w.vs + w.B;
-  // fetch assignment: A slice 128 x 16 = 512 float4 (row mm, k4), B slice 16 x 128 = 512 float4 (k, col4)
-  f4v ra[2], rb[2];
-  auto fetch = [&](int32_t k0) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int idx = tid + q * 256;
-      const int mm = idx / 4, k4 = idx % 4;
-      const int64_t m = m0 + mm;
-      const int32_t k = k0 + 4 * k4;
-      f4v va = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (m < M) {
-        if (k + 3 < K) {
-          va = *(const __attribute__((address_space(1))) f4v*)(A + m * K + k);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) va[e] = k + e < K ? A[m * K + k + e] : 0.0f;
-        }
-      }
-      ra[q] = va;
-      const int kb = idx / 32, j4 = idx % 32;
-      const int32_t kx = k0 + kb;
-      const int64_t c = c0 + 4 * j4;
-      f4v vb = {0.0f, 0.0f, 0.0f, 0.0f};
-      if (kx < K) {
-        if (c + 3 < N) {
-          vb = *(const f4v*)(X + (int64_t)kx * w.vs + c);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) vb[e] = c + e < N ? X[(int64_t)kx * w.vs + c + e] : 0.0f;
-        }
-      }
-      rb[q] = vb;
-    }
-  };
-  auto stash = [&](int buf) {
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int idx = tid + q * 256;
-      const int mm = idx / 4, k4 = idx % 4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) As[buf][4 * k4 + e][mm] = ra[q][e];
-      const int kb = idx / 32, j4 = idx % 32;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) Bs[buf][kb][4 * j4 + e] = rb[q][e];
-    }
-  };
-  mfma_f16x acc[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-  fetch(0);
-  stash(0);
-  __syncthreads();
-  int buf = 0;
-  for (int32_t k0 = 0; k0 < K; k0 += kG2K) {
-    const bool more = k0 + kG2K < K;
-    if (more) fetch(k0 + kG2K);
-#pragma unroll
-    for (int kk = 0; kk < kG2K; kk += 2) {
-      float a[2], b[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = As[buf][kk + lane / 32][wm * 64 + i * 32 + lane % 32];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = Bs[buf][kk + lane / 32][wn * 64 + j * 32 + lane % 32];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
-    if (more) stash(buf ^ 1);
-    __syncthreads();
-    buf ^= 1;
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int64_t m = m0 + wm * 64 + i * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
-        const int64_t c = c0 + wn * 64 + j * 32 + lane % 32;
-        if (m < M && c < N) C[m * w.vs + c] += acc[i][j][v];
-      }
+// Products with fewer 128 x 128 tiles than CUs, few rows or a short K: 64 x 64
+// tiles alone, in slices of 32 k (a wavefront has one accumulator tile here, so
+// a slice of 16 would not cover the loads' latency).
+template <bool VEC>
+__global__ void __launch_bounds__(256, 4) k_w_gemm(WView w, int32_t M, int32_t K, int32_t ntiles, int32_t nops,
+                                                   const float* P, const int32_t* x_row,
+                                                   const int32_t* d_row, int xblk, int store) {
+  __shared__ __attribute__((aligned(16))) float As[2 * 32 * 68], Bs[2 * 32 * 68];
+  const TileIdx t = xcd_tile((uint32_t)((M + 63) / 64), ntiles, nops, blockIdx.x);
+  if (!t.live) return;
+  const float* X = w.va + (int64_t)G(x_row)[t.op] * w.vs + (int64_t)xblk * w.B;
+  float* C = w.va + (int64_t)G(d_row)[t.op] * w.vs + w.B;
+  gemm_tile<64, 64, 32, VEC>(w, M, K, P + (int64_t)t.op * packed_elems(M, K), X, C, (int64_t)t.mt * 64,
+                             (int64_t)t.nt * 64, store, As, Bs);
 }
 
 // The same products with bf16 inputs and fp32 accumulation (v_mfma_f32_32x32x16_bf16):
@@ -1075,11 +1076,6 @@ __global__ void __launch_bounds__(256, 4) k_w_gemm2(WView w, int32_t M, int32_t 
 // B % 4 == 0.
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int kGbM = 128, kGbN = 128, kGbK = 32, kGbP = 40, kGbU = kGbK / 16;
-static_assert(kGemmBK == kG2K && kGemmBK * (kGemmBM + 4) <= 2 * kG2K * (kG2M + 4) &&
-                  kGemmBK * (kGemmBN + 4) <= 2 * kG2K * (kG2N + 4),
-              "the tail tiles of k_w_gemm2 add k in the same slices and fit its LDS arrays");
-static_assert(kGbM == kG2M && kGbN == kG2N, "the two large-product kernels share their tile grid");
-
 __global__ void __launch_bounds__(256, 3) k_w_gemm_bf16(WView w, int32_t M, int32_t K, int32_t mtiles,
                                                      int32_t ntiles, int32_t nops, const uint16_t* W16,
                                                      const int32_t* x_row, const int32_t* d_row, int xblk) {

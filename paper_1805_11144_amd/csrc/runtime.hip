@@ -78,6 +78,9 @@ struct Launch {
   int32_t xs = 1, js = 1;            // LDS row strides of the inputs and currents (padded)
   size_t lds = 0;
   const uint16_t* w16 = nullptr;     // DOT_INC on bf16 MFMA: W rounded to bf16, op k at k*M*K
+  float* wp = nullptr;               // DOT_INC on k_w_gemm, k_w_gemm2: W packed (k_w_pack)
+  int32_t tr = 0;                    // wp: W is stored transposed ([K][M] at w_row)
+  int32_t store = 0;                 // DOT_INC on wp: the products are stored, not added
   // SYN_SCATTER
   const int32_t* syn_seg = nullptr;
   const SynConn* syn_conn = nullptr;
@@ -100,7 +103,7 @@ struct TrainStep {
   int32_t atomic = 0;                // LOWPASS: inputs shared by several rows
   bool dx = false, dw = false;       // DOT_INC: adjoint of the input, gradient of W
   std::vector<Launch> dx_l;          // products on W^T, input rows disjoint within each launch
-  float* wt = nullptr;               // W^T, [nops * K][M]
+  float* wt = nullptr;               // W^T, [nops * K][M] (null: the products read packed weights)
   float* gw = nullptr;               // gradient base of W
 };
 
@@ -188,6 +191,7 @@ struct ms_sim {
   size_t pes_part_n = 0, pes_part_cap = 0;
   // training (window driver)
   bool train_ready = false;
+  bool pack_stale = false;           // weights changed since the forward products' packed weights were made
   std::vector<TrainStep> tsteps;     // backward order
   std::vector<int32_t> trained;      // trained parameter signals
   float* ga = nullptr;               // adjoints, laid out like va
@@ -1135,6 +1139,26 @@ bool bf16_product(const ms_sim* s, const Launch& l) {
   return l.type == OP_DOT_INC && l.a_bcast && l.M >= 64 && l.K >= 16 && l.K % 8 == 0 && s->B % 4 == 0;
 }
 
+// Window products on the MFMA tiles of k_w_gemm and k_w_gemm2, which read packed
+// weights; the others are k_w_gemm_bf16's, k_w_skinny's (few rows, deep K) and
+// k_w_dot's (K < 16).
+bool packed_product(const Launch& l) {
+  return l.type == OP_DOT_INC && !l.w16 && l.K >= 16 && !(l.M <= kSkM && l.K >= 256);
+}
+
+void alloc_packed(ms_sim* s, Launch& l) {
+  l.wp = dev_alloc<float>((size_t)(l.rows * packed_elems(l.M, l.K)));
+  s->extra_allocs.push_back(l.wp);
+}
+
+// (Re)packs a launch's weights as they are now.
+void pack_weights(ms_sim* s, const Launch& l) {
+  const int64_t mt = (l.M + 63) / 64, kt = (l.K + kGemmPadK - 1) / kGemmPadK, n = l.rows * mt * kt;
+  if (n > 2147483647LL) fail(MS_E_INVALID, "product too large for the packed weights' grid");
+  hipLaunchKernelGGL(k_w_pack, dim3((unsigned)n), dim3(256), 0, s->stream, l.a_base, l.w_row, l.M, l.K, (int32_t)mt,
+                     (int32_t)kt, l.tr, l.wp);
+}
+
 // Bit-recorded spike probes: their rows leave the float record (the rows of the
 // other probes keep their places in probe_buf) and their bits go to bits_buf,
 // each probe padded to whole 32-neuron words.
@@ -1205,6 +1229,10 @@ void setup_window(ms_sim* s) {
       HIPCHECK(hipMemcpy(d, w16.data(), w16.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
       l.w16 = d;
     }
+    if (l.rows > 0 && packed_product(l)) {
+      alloc_packed(s, l);
+      pack_weights(s, l);
+    }
   }
   if (s->lds_limit > 65536) {
     const void* wens[] = {(const void*)k_w_ens<1, false, false>, (const void*)k_w_ens<2, false, false>,
@@ -1267,50 +1295,46 @@ void launch_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t
                            l.ptr);
       break;
     case OP_DOT_INC:
-      if (l.w16 || (l.K > 128 && l.M >= 64 && l.K % 4 == 0 && s->B % 4 == 0)) {
-        // 128 x 128 tiles in XCD order: one flat grid padded to a multiple of 8.
-        // Products with K <= 128 are bound by their output traffic and run
-        // faster on the 64 x 64 tiles below (more workgroups in flight).
-        const int32_t mtiles = (l.M + kG2M - 1) / kG2M;
-        const double ntiles = std::ceil(tb / kG2N);
+      if (l.w16) {
+        const int32_t mtiles = (l.M + kGbM - 1) / kGbM;
+        const double ntiles = std::ceil(tb / kGbN);
         const double total = ntiles * mtiles * (double)l.rows;
         if (total >= 2147483648.0 - 8) fail(MS_E_INVALID, "window product too large for the GEMM grid");
-        if (l.w16) {
-          const unsigned grid = (unsigned)(8 * (((int64_t)total + 7) / 8));
-          hipLaunchKernelGGL(k_w_gemm_bf16, dim3(grid), dim3(256), 0, q, w, l.M, l.K, mtiles, (int32_t)ntiles,
-                             (int32_t)l.rows, l.w16, l.x_row, l.d_row, l.src_blk);
-        } else {
-          // tail split: when every tile is resident at once (at most 4 per CU)
-          // and the count is not a whole multiple of the CUs, the column tiles
-          // beyond the last whole multiple run as 64 x 64 tiles
-          const int64_t ncu = std::max<int32_t>(1, s->n_cu), tiles = (int64_t)total;
-          const int64_t per_col = (int64_t)mtiles * l.rows;
-          int64_t nbig = (int64_t)ntiles, small = 0;
-          if (tiles > ncu && tiles <= 4 * ncu && tiles % ncu != 0) {
+        const unsigned grid = (unsigned)(8 * (((int64_t)total + 7) / 8));
+        hipLaunchKernelGGL(k_w_gemm_bf16, dim3(grid), dim3(256), 0, q, w, l.M, l.K, mtiles, (int32_t)ntiles,
+                           (int32_t)l.rows, l.w16, l.x_row, l.d_row, l.src_blk);
+      } else if (l.wp) {
+        const bool vec = s->B % 4 == 0;
+        const int64_t N = (int64_t)T * s->B, mtiles = (l.M + 127) / 128, ntiles = (N + 127) / 128;
+        const int64_t mt64 = (l.M + 63) / 64, nt64 = (N + 63) / 64;
+        const int64_t ncu = std::max<int32_t>(1, s->n_cu), per_col = mtiles * l.rows, tiles = ntiles * per_col;
+        if (mt64 * nt64 * l.rows >= 2147483648LL - 16) fail(MS_E_INVALID, "window product too large for the GEMM grid");
+        if (l.K > 128 && l.M >= 64 && tiles >= ncu) {
+          // 128 x 128 tiles in XCD order, padded to a multiple of 8; column
+          // tiles beyond the last whole multiple of the CUs as 64 x 64 tiles
+          // (past 4 tiles a CU the remainder is under a fifth of the launch)
+          int64_t nbig = ntiles, small = 0;
+          if (tiles <= 4 * ncu && tiles % ncu != 0) {
             const int64_t nb = (tiles / ncu) * ncu / per_col;
             if (nb >= 1 && nb < nbig) {
               nbig = nb;
-              small = (int64_t)((l.M + kGemmBM - 1) / kGemmBM) * l.rows *
-                      (((int64_t)tb - nb * kG2N + kGemmBN - 1) / kGemmBN);
+              small = mt64 * l.rows * ((N - nb * 128 + 63) / 64);
             }
           }
           const int64_t gbig = 8 * ((nbig * per_col + 7) / 8);
-          const unsigned grid = (unsigned)(gbig + 8 * ((small + 7) / 8));
-          hipLaunchKernelGGL(k_w_gemm2, dim3(grid), dim3(256), 0, q, w, l.M, l.K, mtiles, (int32_t)nbig,
-                             (int32_t)l.rows, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk, (uint32_t)gbig);
+          hipLaunchKernelGGL(vec ? k_w_gemm2<true> : k_w_gemm2<false>, dim3((unsigned)(gbig + 8 * ((small + 7) / 8))),
+                             dim3(256), 0, q, w, l.M, l.K, (int32_t)mtiles, (int32_t)nbig, (int32_t)l.rows,
+                             (const float*)l.wp, l.x_row, l.d_row, l.src_blk, (uint32_t)gbig, l.store);
+        } else {
+          hipLaunchKernelGGL(vec ? k_w_gemm<true> : k_w_gemm<false>, dim3((unsigned)(8 * ((mt64 * nt64 * l.rows + 7) / 8))),
+                             dim3(256), 0, q, w, l.M, l.K, (int32_t)nt64, (int32_t)l.rows, (const float*)l.wp, l.x_row,
+                             l.d_row, l.src_blk, l.store);
         }
       } else if (l.M <= kSkM && l.K >= 256) {
         const double ctiles = std::ceil(tb / 64);
         if (ctiles * l.rows >= 2147483648.0) fail(MS_E_INVALID, "window product too large for the grid");
         hipLaunchKernelGGL(k_w_skinny, dim3((unsigned)(ctiles * l.rows)), dim3(64 * kSkW), 0, q, w, l.M, l.K,
                            (int32_t)ctiles, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk);
-      } else if (l.K >= 16) {
-        const int32_t mtiles = (l.M + kGemmBM - 1) / kGemmBM;
-        const double ntiles = std::ceil(tb / kGemmBN);
-        if (ntiles >= 2147483648.0 || (double)mtiles * l.rows > 65535.0)
-          fail(MS_E_INVALID, "window product too large for the GEMM grid");
-        hipLaunchKernelGGL(k_w_gemm, dim3((unsigned)ntiles, (unsigned)(mtiles * l.rows)), dim3(256), 0, q, w, l.M,
-                           l.K, mtiles, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk);
       } else {
         hipLaunchKernelGGL(k_w_dot, dim3(grid_items((double)l.rows * l.M * tb)), dim3(kBlock), 0, q, w, l.rows,
                            l.M, l.K, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk);
@@ -1362,6 +1386,11 @@ void timed_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t 
 void run_window(ms_sim* s, int64_t n_steps) {
   const WindowPlan& w = *s->wplan;
   ensure_window(s, n_steps);
+  if (s->pack_stale) {
+    for (const Launch& l : s->wl)
+      if (l.wp) pack_weights(s, l);
+    s->pack_stale = false;
+  }
   for (int64_t t0 = 0; t0 < n_steps; t0 += s->W) {
     const int32_t T = (int32_t)std::min<int64_t>(s->W, n_steps - t0);
     // phases of one level are independent: spread them over the side streams

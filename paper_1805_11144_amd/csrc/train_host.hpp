@@ -145,8 +145,18 @@ void setup_train(ms_sim* s) {
         st.gw = st.dw ? s->gbase[g.a.base] : nullptr;
         if (st.dx) {
           const int64_t nops = l.rows;
-          st.wt = dev_alloc<float>(std::max<size_t>(1, (size_t)nops * l.M * l.K));
-          s->extra_allocs.push_back(st.wt);
+          // products on packed weights read W itself (k_w_pack transposes); the
+          // others read a transposed copy
+          Launch lt = l;
+          lt.M = l.K;
+          lt.K = l.M;
+          lt.wp = nullptr;
+          lt.store = 0;
+          const bool packed = packed_product(lt);
+          if (!packed) {
+            st.wt = dev_alloc<float>(std::max<size_t>(1, (size_t)nops * l.M * l.K));
+            s->extra_allocs.push_back(st.wt);
+          }
           // ops whose input rows overlap go to different launches, so that each
           // launch adds every adjoint element from one work item
           std::vector<std::vector<int32_t>> colour;
@@ -166,21 +176,20 @@ void setup_train(ms_sim* s) {
           for (const auto& ops : colour) {
             std::vector<int32_t> wr, xr, dr;
             for (int32_t op : ops) {
-              wr.push_back(op * l.K);          // op's W^T block: rows op*K .. of M values
+              wr.push_back(packed ? g.w_row[op] : op * l.K);   // op's block of W, or of W^T: rows op*K .. of M values
               xr.push_back(g.d_row[op]);       // reads the output adjoint
               dr.push_back(g.x_row[op]);       // adds into the input adjoint
             }
-            Launch lx = l;
-            lx.M = l.K;
-            lx.K = l.M;
+            Launch lx = lt;
             lx.rows = (int64_t)ops.size();
-            lx.a_base = st.wt;
+            lx.a_base = packed ? l.a_base : st.wt;
             lx.a_bcast = true;
-            lx.w16 = nullptr;
+            lx.tr = packed ? 1 : 0;
             lx.src_blk = 1;
             lx.w_row = upload_ints(s, wr);
             lx.x_row = upload_ints(s, xr);
             lx.d_row = upload_ints(s, dr);
+            if (packed) alloc_packed(s, lx);
             st.dx_l.push_back(lx);
           }
         }
@@ -278,10 +287,15 @@ void run_backward(ms_sim* s, int32_t T) {
         }
         if (st.dx) {
           time_begin(s, kTimeGradX, q);
-          const int64_t n = nops * l.M * l.K;
-          hipLaunchKernelGGL(k_t_transpose, dim3(grid_for(n)), dim3(kBlock), 0, q, l.a_base, l.w_row, l.M, l.K, n,
-                             st.wt);
-          for (const Launch& lx : st.dx_l) launch_phase(s, lx, T, 0, q, s->ga);
+          if (st.wt) {
+            const int64_t n = nops * l.M * l.K;
+            hipLaunchKernelGGL(k_t_transpose, dim3(grid_for(n)), dim3(kBlock), 0, q, l.a_base, l.w_row, l.M, l.K, n,
+                               st.wt);
+          }
+          for (const Launch& lx : st.dx_l) {
+            if (lx.wp) pack_weights(s, lx);
+            launch_phase(s, lx, T, 0, q, s->ga);
+          }
           time_end(s, q);
         }
         break;
@@ -407,6 +421,7 @@ ms_status ms_sim_train_step(ms_sim* s, int64_t n_steps, const ms_feed* feeds, in
                            (const float*)(s->gbase[sg.base] + off), n, (float)learning_rate);
       }
       time_end(s, s->stream);
+      s->pack_stale = true;
     }
     HIPCHECK(hipGetLastError());
     HIPCHECK(hipEventRecord(s->ev1, s->stream));
@@ -462,6 +477,7 @@ ms_status ms_sim_set_train_param(ms_sim* s, int32_t which, int32_t id, int32_t f
     }
     HIPCHECK(hipStreamSynchronize(s->stream));
     HIPCHECK(hipMemcpy(t.p, h.data(), (size_t)n * 4, hipMemcpyHostToDevice));
+    s->pack_stale = true;
   });
 }
 

@@ -1,0 +1,29 @@
+"""GPU: the window driver's fp32 products at the edges of their tiles.
+
+A product's tiles (128 x 128, 64 x 64, slices of 16 or 32 k, packed weights
+padded to whole tiles) add every sum over k in order into one accumulator, as
+the time-major driver's one-thread-per-row products do, so rate-neuron layers
+fed by them must agree with that driver bit for bit.  Sizes: rows and inputs
+one below, at and one above a tile or slice edge; minibatches with and without
+16-byte aligned columns; few and many column tiles (3840 columns on 256 CUs put
+the large shape on 128 x 128 tiles)."""
+import numpy as np
+import pytest
+
+import paper_1805_11144_amd as M
+from synth import make_workload
+from tests.test_gpu_parity import run_gpu
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(n_in, hidden, batch, 6) for n_in in (15, 16, 31, 33) for hidden in (63, 65) for batch in (5, 8)]
+SHAPES += [(129, 128, 7, 9), (130, 129, 12, 11), (257, 193, 12, 5), (1000, 64, 5, 3), (144, 1100, 12, 320)]
+
+
+@pytest.mark.parametrize("n_in,hidden,batch,steps", SHAPES)
+def test_products_equal_time_major(n_in, hidden, batch, steps):
+    w = make_workload("c3", neuron_type="relu", n_steps=steps, minibatch=batch, n_hidden=hidden, n_in=n_in, n_out=3)
+    got, ref = run_gpu(w, driver=M.DRIVER_WINDOW), run_gpu(w, driver=M.DRIVER_STEPS)
+    for p in (1, 2):   # the two hidden layers
+        assert np.abs(ref[p]).max() > 0
+        assert np.array_equal(got[p], ref[p]), (p, np.abs(got[p] - ref[p]).max())
