@@ -577,11 +577,13 @@ bool Fuser::fuse_with(int32_t ci, std::vector<LGroup>& out, LGroup& prologue) {
 
   // the rest of the step: resets without the post inputs and the folded
   // filter inputs, no CopyInc, DotIncs without the folded ops
-  std::vector<char> drop_row((size_t)nrows, 0);
+  // (an increment of a post input after the copy stays: it adds to the sum
+  // that the end of the previous step left there)
+  std::vector<char> drop_row((size_t)nrows, 0), fold_row((size_t)nrows, 0);
   for (int64_t u = 0; u < C.rows; ++u) drop_row[lrow(C.dst, u)] = 1;
   for (int64_t r = 0; r < nl; ++r) {
     const int64_t v = lrow(L.src, r);
-    if (folded(v)) drop_row[v] = 1;
+    if (folded(v)) drop_row[v] = fold_row[v] = 1;
   }
   out.clear();
   for (int32_t g = 0; g + 1 < n; ++g) {
@@ -614,7 +616,7 @@ bool Fuser::fuse_with(int32_t ci, std::vector<LGroup>& out, LGroup& prologue) {
       bool any = false;
       for (int64_t u = 0; u < q.rows; ++u) {
         const int64_t x = lrow(q.dst, u);
-        if (drop_row[x]) { any = true; continue; }
+        if (fold_row[x]) { any = true; continue; }
         const int64_t e0 = q.ptr.empty() ? u : q.ptr[u], e1 = q.ptr.empty() ? u + 1 : q.ptr[u + 1];
         dst.push_back((int32_t)x);
         for (int64_t e = e0; e < e1; ++e) {
@@ -629,7 +631,7 @@ bool Fuser::fuse_with(int32_t ci, std::vector<LGroup>& out, LGroup& prologue) {
       k.ops.clear();
       for (int32_t oi : q.ops) {
         const Op& o = p.ir.ops[oi];
-        if (!drop_row[p.sig_offset[o.dst.sig] + o.dst.start]) k.ops.push_back(oi);
+        if (!fold_row[p.sig_offset[o.dst.sig] + o.dst.start]) k.ops.push_back(oi);
       }
       if (k.ops.empty()) k.ops.push_back(q.ops[0]);
       k.rows = (int64_t)dst.size();
