@@ -299,6 +299,29 @@ struct WindowPlan {
 
 WindowPlan make_window_plan(const Plan& p);
 
+// How the window driver runs one phase (fuse_window): the phase's group with
+// its operand rows, and what it took over from others.
+struct WRun {
+  LGroup g;
+  int32_t src_blk = 1, a_blk = 1;
+  bool skip = false;            // another phase does this one's work
+  // increments: 0 adds to the rows as they are; 1 starts from init_vals (one
+  // per written row, empty: zero); 2 from the parameter rows init_src.  Neuron
+  // phases with jx: the value that their input current starts from
+  int32_t init = 0;
+  std::vector<float> init_vals;
+  LOperand init_src;
+  // LIF, LIF_RATE (jx.base >= 0): the input current is computed here, J =
+  // init + ja (.) jx, jx read at block offset jx_blk
+  LOperand jx, ja;
+  int32_t jx_blk = 1;
+  // LIF (fy.base >= 0): jx is the input v of the filter y <- fa y + fb v with
+  // state rows fy, and the current reads y as the previous step left it
+  LOperand fy;
+  std::vector<float> fa, fb;
+};
+std::vector<WRun> fuse_window(const Plan& p, const WindowPlan& w);
+
 // ------------------------------------------------- time-major step program
 // The groups one timestep of the launch drivers (plain launches, hipGraph)
 // runs, in order.  Consecutive independent fused-ensemble groups share a

@@ -59,12 +59,22 @@ __global__ void k_w_copy(WView w, int64_t rows, Opnd dst, const float* param, Op
   w.va[vat(w, rowof(dst, _r), w.B + _c)] = w_src(w, param, bcast, rowof(src, _r), sblk, _c);
 }
 
+// What an increment starts from: the destination as it is (mode 0), or, when the
+// reset or parameter copy before it was dropped, a value per row (null: zero).
+struct WInit {
+  const float* p;
+  Opnd row;
+  int32_t mode;
+};
+
+__device__ __forceinline__ float w_init(const WInit& in, uint32_t r) { return in.p ? G(in.p)[rowof(in.row, r)] : 0.0f; }
+
 // dst += sum of the src entries of unique destination u (ptr == null: one entry)
 __global__ void k_w_copy_inc(WView w, int64_t rows, Opnd dst, const float* param, Opnd src, int bcast, int sblk,
-                             const int32_t* ptr) {
+                             const int32_t* ptr, WInit init) {
   W_ITEM(rows);
   const int64_t di = vat(w, rowof(dst, _r), w.B + _c);
-  float acc = w.va[di];
+  float acc = init.mode ? w_init(init, _r) : w.va[di];
   if (ptr) {
     for (int32_t e = G(ptr)[_r]; e < G(ptr)[_r + 1]; ++e) acc += w_src(w, param, bcast, rowof(src, e), sblk, _c);
   } else {
@@ -75,10 +85,10 @@ __global__ void k_w_copy_inc(WView w, int64_t rows, Opnd dst, const float* param
 
 // dst += a (.) x, entries grouped by destination as in k_w_copy_inc
 __global__ void k_w_elem_inc(WView w, int64_t rows, Opnd dst, const float* a_param, Opnd a, int a_bcast, int ablk,
-                             const float* x_param, Opnd x, int x_bcast, int xblk, const int32_t* ptr) {
+                             const float* x_param, Opnd x, int x_bcast, int xblk, const int32_t* ptr, WInit init) {
   W_ITEM(rows);
   const int64_t di = vat(w, rowof(dst, _r), w.B + _c);
-  float acc = w.va[di];
+  float acc = init.mode ? w_init(init, _r) : w.va[di];
   if (ptr) {
     for (int32_t e = G(ptr)[_r]; e < G(ptr)[_r + 1]; ++e)
       acc += w_src(w, a_param, a_bcast, rowof(a, e), ablk, _c) * w_src(w, x_param, x_bcast, rowof(x, e), xblk, _c);
@@ -90,7 +100,7 @@ __global__ void k_w_elem_inc(WView w, int64_t rows, Opnd dst, const float* a_par
 
 // dst[m] += W[m, :] . x for every op, output row and (step, column)
 __global__ void k_w_dot(WView w, int64_t nops, int32_t M, int32_t K, const float* Wt, const int32_t* w_row,
-                        const int32_t* x_row, const int32_t* d_row, int xblk) {
+                        const int32_t* x_row, const int32_t* d_row, int xblk, int store) {
   W_ITEM(nops * M);
   const uint32_t op = _r / (uint32_t)M, m = _r - op * (uint32_t)M;
   gptr<float> wr = G(Wt) + ((int64_t)G(w_row)[op] + m) * K;
@@ -98,15 +108,39 @@ __global__ void k_w_dot(WView w, int64_t nops, int32_t M, int32_t K, const float
   const int64_t xc = (int64_t)xblk * w.B + _c;
   float acc = 0.0f;
   for (int32_t k = 0; k < K; ++k) acc += wr[k] * w.va[vat(w, x0 + k, xc)];
-  w.va[vat(w, (int64_t)G(d_row)[op] + m, w.B + _c)] += acc;
+  float& d = w.va[vat(w, (int64_t)G(d_row)[op] + m, w.B + _c)];
+  d = (store ? 0.0f : d) + acc;
 }
 
-__global__ void k_w_lif_rate(WView w, int64_t rows, Opnd J, Opnd s, NeuronParams np, int jblk) {
+// A neuron phase's input current when the phase computes it itself: J = init +
+// a x, the fma of the increment it replaces (IN = 1); with a filter (IN = 2,
+// neurons that run step after step) x is that filter's output as the previous
+// step left it and the rows hold the filter's input.  A layer of spiking
+// neurons behind a filtered product took passes for the reset to the bias, the
+// filter, the scaled sum and the neurons, ten reads or writes of the layer's
+// signals; here it is one read and one write.
+struct WCurrent {
+  Opnd x, a, y;
+  int32_t blk, store;          // store: J is also stored (the backward pass reads it)
+  const float* ap;
+  WInit init;
+  const float *fa, *fb;        // per row
+};
+
+template <int IN>
+__global__ void k_w_lif_rate(WView w, int64_t rows, Opnd J, Opnd s, NeuronParams np, int jblk, WCurrent in) {
   W_ITEM(rows);
   const float tau_rc = np.tau_rc_r ? G(np.tau_rc_r)[_r] : np.tau_rc;
   const float tau_ref = np.tau_ref_r ? G(np.tau_ref_r)[_r] : np.tau_ref;
   const float amp = np.amp_r ? G(np.amp_r)[_r] : np.amp;
-  const float j = w.va[vat(w, rowof(J, _r), (int64_t)jblk * w.B + _c)];
+  const int64_t jo = vat(w, rowof(J, _r), (int64_t)jblk * w.B + _c);
+  float j;
+  if constexpr (IN != 0) {
+    j = fmaf(G(in.ap)[rowof(in.a, _r)], w.va[vat(w, rowof(in.x, _r), (int64_t)in.blk * w.B + _c)], w_init(in.init, _r));
+    if (in.store) w.va[jo] = j;
+  } else {
+    j = w.va[jo];
+  }
   float out = 0.0f;
   if (np.relu) {
     out = amp * fmaxf(j, 0.0f);
@@ -125,8 +159,10 @@ __global__ void k_w_lif_rate(WView w, int64_t rows, Opnd J, Opnd s, NeuronParams
   if (_i >= (uint32_t)(rows) * (uint32_t)w.B) return;                          \
   const uint32_t _r = _i / (uint32_t)w.B, _b = _i - _r * (uint32_t)w.B;
 
+// Eight steps' inputs are loaded before they are used.
+template <int IN>
 __global__ void k_w_lif(WView w, int64_t rows, Opnd J, Opnd s, Opnd V, Opnd R, float* pa, NeuronParams np,
-                        float dt, int jblk) {
+                        float dt, int jblk, WCurrent in) {
   W_ROWCOL(rows);
   const float tau_rc = np.tau_rc_r ? G(np.tau_rc_r)[_r] : np.tau_rc;
   const float tau_ref = np.tau_ref_r ? G(np.tau_ref_r)[_r] : np.tau_ref;
@@ -134,23 +170,51 @@ __global__ void k_w_lif(WView w, int64_t rows, Opnd J, Opnd s, Opnd V, Opnd R, f
   const float full = np.full_r ? G(np.full_r)[_r] : np.full;
   const int64_t vi = rowof(V, _r) * w.B + _b, ri = rowof(R, _r) * w.B + _b;
   float v = pa[vi], rf = pa[ri];
-  const int64_t jr = rowof(J, _r) * w.vs + (int64_t)jblk * w.B + _b;
-  const int64_t sr = rowof(s, _r) * w.vs + w.B + _b;
+  const float* xp = w.va + (IN ? rowof(in.x, _r) * w.vs + (int64_t)in.blk * w.B
+                               : rowof(J, _r) * w.vs + (int64_t)jblk * w.B) + _b;
+  float* sp = w.va + rowof(s, _r) * w.vs + w.B + _b;
   const float inv_tau = 1.0f / tau_rc;
+  float gain = 0.0f, bias = 0.0f, fa = 0.0f, fb = 0.0f, y = 0.0f;
+  if constexpr (IN != 0) {
+    gain = G(in.ap)[rowof(in.a, _r)];
+    bias = w_init(in.init, _r);
+  }
+  if constexpr (IN == 2) {
+    fa = G(in.fa)[_r];
+    fb = G(in.fb)[_r];
+    y = w.va[rowof(in.y, _r) * w.vs + _b];
+  }
+  auto current = [&](float x) {
+    if constexpr (IN == 0) {
+      return x;
+    } else if constexpr (IN == 1) {
+      return fmaf(gain, x, bias);
+    } else {
+      const float j = fmaf(gain, y, bias);
+      y = lowpass_step(fa, y, fb, x);
+      return j;
+    }
+  };
+  auto sweep = [&](auto upd) {
+    int32_t t = 0;
+    for (; t + 8 <= w.T; t += 8) {
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = xp[(int64_t)(t + u) * w.B];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) sp[(int64_t)(t + u) * w.B] = upd(current(x[u]));
+    }
+    for (; t < w.T; ++t) sp[(int64_t)t * w.B] = upd(current(xp[(int64_t)t * w.B]));
+  };
   if (dt * inv_tau <= 0.0625f) {
     const float amp_dt = amp / dt, tau6 = tau_rc * (1.0f / 6.0f);
-    for (int32_t t = 0; t < w.T; ++t) {
-      const float j = w.va[jr + (int64_t)t * w.B];
-      w.va[sr + (int64_t)t * w.B] = lif_update_bf(j, v, rf, tau6, tau_ref, amp_dt, dt, inv_tau);
-    }
+    sweep([&](float j) { return lif_update_bf(j, v, rf, tau6, tau_ref, amp_dt, dt, inv_tau); });
   } else {
-    for (int32_t t = 0; t < w.T; ++t) {
-      const float j = w.va[jr + (int64_t)t * w.B];
-      w.va[sr + (int64_t)t * w.B] = neuron_update(0, j, v, rf, tau_rc, tau_ref, amp, full, dt, inv_tau);
-    }
+    sweep([&](float j) { return neuron_update(0, j, v, rf, tau_rc, tau_ref, amp, full, dt, inv_tau); });
   }
   pa[vi] = v;
   pa[ri] = rf;
+  if constexpr (IN == 2) w.va[rowof(in.y, _r) * w.vs + (int64_t)w.T * w.B + _b] = y;
 }
 
 // y(t) = a y(t - 1) + b v(t) through the window; y(-1) is block 0
@@ -946,7 +1010,7 @@ constexpr int kSkM = 16, kSkW = 8;
 
 __global__ void __launch_bounds__(512) k_w_skinny(WView w, int32_t M, int32_t K, int32_t ctiles, const float* Wt,
                                                   const int32_t* w_row, const int32_t* x_row, const int32_t* d_row,
-                                                  int xblk) {
+                                                  int xblk, int store) {
   __shared__ float red[kSkW][kSkM][64];
   const int64_t N = (int64_t)w.T * w.B;
   const int op = blockIdx.x / ctiles;
@@ -1001,7 +1065,7 @@ __global__ void __launch_bounds__(512) k_w_skinny(WView w, int32_t M, int32_t K,
     float sum = 0.0f;
 #pragma unroll
     for (int v = 0; v < kSkW; ++v) sum += red[v][m][l];
-    if (c0 + l < N) C[(int64_t)m * w.vs + c0 + l] += sum;
+    if (c0 + l < N) C[(int64_t)m * w.vs + c0 + l] = (store ? 0.0f : C[(int64_t)m * w.vs + c0 + l]) + sum;
   }
 }
 
@@ -1078,7 +1142,7 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int kGbM = 128, kGbN = 128, kGbK = 32, kGbP = 40, kGbU = kGbK / 16;
 __global__ void __launch_bounds__(256, 3) k_w_gemm_bf16(WView w, int32_t M, int32_t K, int32_t mtiles,
                                                      int32_t ntiles, int32_t nops, const uint16_t* W16,
-                                                     const int32_t* x_row, const int32_t* d_row, int xblk) {
+                                                     const int32_t* x_row, const int32_t* d_row, int xblk, int store) {
   __shared__ __attribute__((aligned(16))) __bf16 As[2][kGbM][kGbP];
   __shared__ __attribute__((aligned(16))) __bf16 Bs[2][kGbN][kGbP];
   const TileIdx ti = xcd_tile(mtiles, ntiles, nops, blockIdx.x);
@@ -1161,7 +1225,7 @@ __global__ void __launch_bounds__(256, 3) k_w_gemm_bf16(WView w, int32_t M, int3
       for (int v = 0; v < 16; ++v) {
         const int64_t m = m0 + wm * 64 + i * 32 + 8 * (v / 4) + 4 * (lane / 32) + (v % 4);
         const int64_t c = c0 + wn * 64 + j * 32 + lane % 32;
-        if (m < M && c < N) C[m * w.vs + c] += acc[i][j][v];
+        if (m < M && c < N) C[m * w.vs + c] = (store ? 0.0f : C[m * w.vs + c]) + acc[i][j][v];
       }
 }
 
@@ -1211,15 +1275,19 @@ __global__ void k_w_feed4(WView w, int64_t rows, Opnd dst, const int32_t* feed_r
   w4(w, rowof(dst, _r), w.B + _c) = *(const w_f4*)(stage + ((t0 + t) * feed_rows + G(feed_row)[_r]) * w.B + b);
 }
 
-// k_w_elem_inc, four entries per thread (each entry the same sum, in the same order)
-__global__ void k_w_elem_inc4(WView w, int64_t rows, Opnd dst, const float* a_param, Opnd a, int a_bcast, int ablk,
-                              const float* x_param, Opnd x, int x_bcast, int xblk, const int32_t* ptr);
+__device__ __forceinline__ w_f4 w_init4(const WInit& in, uint32_t r, const w_f4& d) {
+  if (!in.mode) return d;
+  const float v = w_init(in, r);
+  return w_f4{v, v, v, v};
+}
 
+// k_w_copy_inc and k_w_elem_inc, four entries per thread (each entry the same
+// sum, in the same order)
 __global__ void k_w_copy_inc4(WView w, int64_t rows, Opnd dst, const float* param, Opnd src, int bcast, int sblk,
-                              const int32_t* ptr) {
+                              const int32_t* ptr, WInit init) {
   W_ITEM4(rows);
   w_f4& d = w4(w, rowof(dst, _r), w.B + _c);
-  w_f4 acc = d;
+  w_f4 acc = w_init4(init, _r, d);
   if (ptr) {
     for (int32_t e = G(ptr)[_r]; e < G(ptr)[_r + 1]; ++e) acc += w_src4(w, param, bcast, rowof(src, e), sblk, _c);
   } else {
@@ -1229,10 +1297,10 @@ __global__ void k_w_copy_inc4(WView w, int64_t rows, Opnd dst, const float* para
 }
 
 __global__ void k_w_elem_inc4(WView w, int64_t rows, Opnd dst, const float* a_param, Opnd a, int a_bcast, int ablk,
-                              const float* x_param, Opnd x, int x_bcast, int xblk, const int32_t* ptr) {
+                              const float* x_param, Opnd x, int x_bcast, int xblk, const int32_t* ptr, WInit init) {
   W_ITEM4(rows);
   w_f4& d = w4(w, rowof(dst, _r), w.B + _c);
-  w_f4 acc = d;
+  w_f4 acc = w_init4(init, _r, d);
   if (ptr) {
     for (int32_t e = G(ptr)[_r]; e < G(ptr)[_r + 1]; ++e)
       acc += w_src4(w, a_param, a_bcast, rowof(a, e), ablk, _c) * w_src4(w, x_param, x_bcast, rowof(x, e), xblk, _c);

@@ -80,7 +80,10 @@ struct Launch {
   const uint16_t* w16 = nullptr;     // DOT_INC on bf16 MFMA: W rounded to bf16, op k at k*M*K
   float* wp = nullptr;               // DOT_INC on k_w_gemm, k_w_gemm2: W packed (k_w_pack)
   int32_t tr = 0;                    // wp: W is stored transposed ([K][M] at w_row)
-  int32_t store = 0;                 // DOT_INC on wp: the products are stored, not added
+  bool skip = false;                 // another phase does this one's work (kept for the backward pass)
+  WInit init{};                      // increments: what they start from (DOT_INC: mode only)
+  int32_t cur_in = 0;                // LIF, LIF_RATE: 1, 2: the phase computes its input current from `cur`
+  WCurrent cur{};
   // SYN_SCATTER
   const int32_t* syn_seg = nullptr;
   const SynConn* syn_conn = nullptr;
@@ -1193,6 +1196,49 @@ static void setup_spike_bits(ms_sim* s, const WindowPlan& w) {
   }
 }
 
+// Uploads an array the simulator keeps until it is destroyed.
+template <class T>
+T* upload(ms_sim* s, const std::vector<T>& v) {
+  T* d = dev_alloc<T>(std::max<size_t>(1, v.size()));
+  s->extra_allocs.push_back(d);
+  if (!v.empty()) HIPCHECK(hipMemcpy(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+  return d;
+}
+
+Opnd upload_operand(ms_sim* s, const LOperand& o) {
+  return o.idx.empty() ? Opnd{nullptr, o.start} : Opnd{upload(s, o.idx), 0};
+}
+
+// What a window phase took over from others (fuse_window).
+void setup_run(ms_sim* s, Launch& l, const WRun& r) {
+  l.src_blk = r.src_blk;
+  l.a_blk = r.a_blk;
+  l.skip = r.skip;
+  WInit init{};
+  init.mode = r.init;
+  if (r.init == 2) {
+    init.p = s->base_ptr[r.init_src.base];
+    init.row = upload_operand(s, r.init_src);
+  } else if (!r.init_vals.empty()) {
+    init.p = upload(s, r.init_vals);
+  }
+  if (r.jx.base < 0) {
+    l.init = init;
+    return;
+  }
+  l.cur_in = r.fy.base >= 0 ? 2 : 1;
+  l.cur.x = upload_operand(s, r.jx);
+  l.cur.blk = r.jx_blk;
+  l.cur.a = upload_operand(s, r.ja);
+  l.cur.ap = s->base_ptr[r.ja.base];
+  l.cur.init = init;
+  if (r.fy.base >= 0) {
+    l.cur.y = upload_operand(s, r.fy);
+    l.cur.fa = upload(s, r.fa);
+    l.cur.fb = upload(s, r.fb);
+  }
+}
+
 void setup_window(ms_sim* s) {
   WindowPlan& w = *s->wplan;
   const int32_t B = s->B;
@@ -1205,20 +1251,20 @@ void setup_window(ms_sim* s) {
   ensure_window(s, 1);
   for (int k = 0; k < ms_sim::kSide; ++k) HIPCHECK(hipStreamCreateWithFlags(&s->side[k], hipStreamNonBlocking));
   for (int k = 0; k <= ms_sim::kSide; ++k) HIPCHECK(hipEventCreateWithFlags(&s->side_ev[k], hipEventDisableTiming));
+  const std::vector<WRun> runs = fuse_window(*s->plan, w);
   std::vector<LGroup> groups;
-  for (const WPhase& ph : w.phases) groups.push_back(ph.g);
+  for (const WRun& r : runs) groups.push_back(r.g);
   build_launches(s, groups, s->wl, w.probe_rows, &s->wprobe_src);
   if (!s->spike_mag.empty()) setup_spike_bits(s, w);
   for (size_t k = 0; k < s->wl.size(); ++k) {
     Launch& l = s->wl[k];
-    l.src_blk = w.phases[k].src_blk;
-    l.a_blk = w.phases[k].a_blk;
+    setup_run(s, l, runs[k]);
     if (l.type == OP_ENS) {
-      ens_shape(s, l, w.phases[k].g);
+      ens_shape(s, l, runs[k].g);
     }
     if (s->gemm_dtype == MS_GEMM_BF16 && bf16_product(s, l)) {
       // each op's [M][K] block of W, rounded to nearest even, packed op after op
-      const LGroup& g = w.phases[k].g;
+      const LGroup& g = runs[k].g;
       const std::vector<float>& hw = host_param_base(s, g.a.base);
       std::vector<uint16_t> w16((size_t)l.rows * l.M * l.K);
       for (int64_t op = 0; op < l.rows; ++op)
@@ -1279,20 +1325,20 @@ void launch_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t
     case OP_COPY_INC:
       if (s->B % 4 == 0)
         hipLaunchKernelGGL(k_w_copy_inc4, dim3(grid_items(l.rows * tb / 4)), dim3(kBlock), 0, q, w, l.rows, l.dst,
-                           l.src_base, l.src, (int)l.src_bcast, l.src_blk, l.ptr);
+                           l.src_base, l.src, (int)l.src_bcast, l.src_blk, l.ptr, l.init);
       else
         hipLaunchKernelGGL(k_w_copy_inc, dim3(grid_items(l.rows * tb)), dim3(kBlock), 0, q, w, l.rows, l.dst,
-                           l.src_base, l.src, (int)l.src_bcast, l.src_blk, l.ptr);
+                           l.src_base, l.src, (int)l.src_bcast, l.src_blk, l.ptr, l.init);
       break;
     case OP_ELEM_INC:
       if (s->B % 4 == 0)
         hipLaunchKernelGGL(k_w_elem_inc4, dim3(grid_items(l.rows * tb / 4)), dim3(kBlock), 0, q, w, l.rows, l.dst,
                            l.a_base, l.a, (int)l.a_bcast, l.a_blk, l.src_base, l.src, (int)l.src_bcast, l.src_blk,
-                           l.ptr);
+                           l.ptr, l.init);
       else
         hipLaunchKernelGGL(k_w_elem_inc, dim3(grid_items(l.rows * tb)), dim3(kBlock), 0, q, w, l.rows, l.dst,
                            l.a_base, l.a, (int)l.a_bcast, l.a_blk, l.src_base, l.src, (int)l.src_bcast, l.src_blk,
-                           l.ptr);
+                           l.ptr, l.init);
       break;
     case OP_DOT_INC:
       if (l.w16) {
@@ -1302,7 +1348,7 @@ void launch_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t
         if (total >= 2147483648.0 - 8) fail(MS_E_INVALID, "window product too large for the GEMM grid");
         const unsigned grid = (unsigned)(8 * (((int64_t)total + 7) / 8));
         hipLaunchKernelGGL(k_w_gemm_bf16, dim3(grid), dim3(256), 0, q, w, l.M, l.K, mtiles, (int32_t)ntiles,
-                           (int32_t)l.rows, l.w16, l.x_row, l.d_row, l.src_blk);
+                           (int32_t)l.rows, l.w16, l.x_row, l.d_row, l.src_blk, l.init.mode);
       } else if (l.wp) {
         const bool vec = s->B % 4 == 0;
         const int64_t N = (int64_t)T * s->B, mtiles = (l.M + 127) / 128, ntiles = (N + 127) / 128;
@@ -1324,30 +1370,34 @@ void launch_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t
           const int64_t gbig = 8 * ((nbig * per_col + 7) / 8);
           hipLaunchKernelGGL(vec ? k_w_gemm2<true> : k_w_gemm2<false>, dim3((unsigned)(gbig + 8 * ((small + 7) / 8))),
                              dim3(256), 0, q, w, l.M, l.K, (int32_t)mtiles, (int32_t)nbig, (int32_t)l.rows,
-                             (const float*)l.wp, l.x_row, l.d_row, l.src_blk, (uint32_t)gbig, l.store);
+                             (const float*)l.wp, l.x_row, l.d_row, l.src_blk, (uint32_t)gbig, l.init.mode);
         } else {
           hipLaunchKernelGGL(vec ? k_w_gemm<true> : k_w_gemm<false>, dim3((unsigned)(8 * ((mt64 * nt64 * l.rows + 7) / 8))),
                              dim3(256), 0, q, w, l.M, l.K, (int32_t)nt64, (int32_t)l.rows, (const float*)l.wp, l.x_row,
-                             l.d_row, l.src_blk, l.store);
+                             l.d_row, l.src_blk, l.init.mode);
         }
       } else if (l.M <= kSkM && l.K >= 256) {
         const double ctiles = std::ceil(tb / 64);
         if (ctiles * l.rows >= 2147483648.0) fail(MS_E_INVALID, "window product too large for the grid");
         hipLaunchKernelGGL(k_w_skinny, dim3((unsigned)(ctiles * l.rows)), dim3(64 * kSkW), 0, q, w, l.M, l.K,
-                           (int32_t)ctiles, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk);
+                           (int32_t)ctiles, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk, l.init.mode);
       } else {
         hipLaunchKernelGGL(k_w_dot, dim3(grid_items((double)l.rows * l.M * tb)), dim3(kBlock), 0, q, w, l.rows,
-                           l.M, l.K, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk);
+                           l.M, l.K, l.a_base, l.w_row, l.x_row, l.d_row, l.src_blk, l.init.mode);
       }
       break;
     case OP_LIF:
-      hipLaunchKernelGGL(k_w_lif, dim3(grid_items((double)l.rows * s->B)), dim3(kBlock), 0, q, w, l.rows, l.src,
-                         l.dst, l.V, l.ref, s->pa, l.np, s->dt, l.src_blk);
+      hipLaunchKernelGGL(l.cur_in == 2 ? k_w_lif<2> : l.cur_in == 1 ? k_w_lif<1> : k_w_lif<0>,
+                         dim3(grid_items((double)l.rows * s->B)), dim3(kBlock), 0, q, w, l.rows, l.src, l.dst, l.V,
+                         l.ref, s->pa, l.np, s->dt, l.src_blk, l.cur);
       break;
-    case OP_LIF_RATE:
-      hipLaunchKernelGGL(k_w_lif_rate, dim3(grid_items(l.rows * tb)), dim3(kBlock), 0, q, w, l.rows, l.src, l.dst,
-                         l.np, l.src_blk);
+    case OP_LIF_RATE: {
+      WCurrent cur = l.cur;
+      cur.store = s->train_ready;
+      hipLaunchKernelGGL(l.cur_in ? k_w_lif_rate<1> : k_w_lif_rate<0>, dim3(grid_items(l.rows * tb)), dim3(kBlock), 0,
+                         q, w, l.rows, l.src, l.dst, l.np, l.src_blk, cur);
       break;
+    }
     case OP_LOWPASS:
       hipLaunchKernelGGL(k_w_lowpass, dim3(grid_items((double)l.rows * s->B)), dim3(kBlock), 0, q, w, l.rows,
                          l.dst, l.src, l.fp, l.src_blk);
@@ -1395,16 +1445,18 @@ void run_window(ms_sim* s, int64_t n_steps) {
     const int32_t T = (int32_t)std::min<int64_t>(s->W, n_steps - t0);
     // phases of one level are independent: spread them over the side streams
     for (size_t a = 0; a < s->wl.size();) {
-      size_t e = a + 1;
-      while (e < s->wl.size() && w.phases[e].level == w.phases[a].level) ++e;
-      if (e - a == 1) {
-        timed_phase(s, s->wl[a], T, t0, s->stream);
+      size_t e = a + 1, live = !s->wl[a].skip;
+      for (; e < s->wl.size() && w.phases[e].level == w.phases[a].level; ++e) live += !s->wl[e].skip;
+      if (live <= 1) {
+        for (size_t i = a; i < e; ++i)
+          if (!s->wl[i].skip) timed_phase(s, s->wl[i], T, t0, s->stream);
       } else {
-        const int used = (int)std::min<size_t>(ms_sim::kSide, e - a - 1);
+        const int used = (int)std::min<size_t>(ms_sim::kSide, live - 1);
         HIPCHECK(hipEventRecord(s->side_ev[ms_sim::kSide], s->stream));
         for (int k = 0; k < used; ++k) HIPCHECK(hipStreamWaitEvent(s->side[k], s->side_ev[ms_sim::kSide], 0));
         size_t rr = 0;   // exclusive phases round-robin over the streams; the rest in order on the main stream
         for (size_t i = a; i < e; ++i) {
+          if (s->wl[i].skip) continue;
           if (!w.phases[i].exclusive) { timed_phase(s, s->wl[i], T, t0, s->stream); continue; }
           const size_t slot = rr++ % (size_t)(used + 1);
           timed_phase(s, s->wl[i], T, t0, slot == 0 ? s->stream : s->side[slot - 1]);

@@ -32,13 +32,6 @@ int32_t trained_kind(const std::string& name) {
   return -1;
 }
 
-int32_t* upload_ints(ms_sim* s, const std::vector<int32_t>& v) {
-  int32_t* d = dev_alloc<int32_t>(std::max<size_t>(1, v.size()));
-  s->extra_allocs.push_back(d);
-  if (!v.empty()) HIPCHECK(hipMemcpy(d, v.data(), v.size() * 4, hipMemcpyHostToDevice));
-  return d;
-}
-
 int64_t lrow(const LOperand& o, int64_t r) { return o.idx.empty() ? o.start + r : o.idx[(size_t)r]; }
 
 bool rows_distinct(std::vector<int64_t> rows) {
@@ -151,7 +144,7 @@ void setup_train(ms_sim* s) {
           lt.M = l.K;
           lt.K = l.M;
           lt.wp = nullptr;
-          lt.store = 0;
+          lt.init = WInit{};
           const bool packed = packed_product(lt);
           if (!packed) {
             st.wt = dev_alloc<float>(std::max<size_t>(1, (size_t)nops * l.M * l.K));
@@ -186,9 +179,9 @@ void setup_train(ms_sim* s) {
             lx.a_bcast = true;
             lx.tr = packed ? 1 : 0;
             lx.src_blk = 1;
-            lx.w_row = upload_ints(s, wr);
-            lx.x_row = upload_ints(s, xr);
-            lx.d_row = upload_ints(s, dr);
+            lx.w_row = upload(s, wr);
+            lx.x_row = upload(s, xr);
+            lx.d_row = upload(s, dr);
             if (packed) alloc_packed(s, lx);
             st.dx_l.push_back(lx);
           }
