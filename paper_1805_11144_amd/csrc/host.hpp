@@ -5,6 +5,7 @@
 #pragma once
 
 #include <cstdint>
+#include <array>
 #include <map>
 #include <memory>
 #include <stdexcept>
@@ -342,6 +343,48 @@ struct LaunchPlan {
 };
 LaunchPlan make_launch_plan(const Plan& p);
 std::vector<LGroup> merge_ens_groups(const std::vector<LGroup>& in);
+
+// ---------------------------------------------------- resident program
+// Tables of k_resident (make_resident): a small model's step for one workgroup
+// per batch column.  Row places are floats of LDS; place 0 holds 1.0.
+constexpr int32_t kResD = 2, kResDec = 2;        // input dimensions, decoded outputs of an ensemble
+constexpr int32_t kResWaves = 8;
+constexpr int32_t kResSlots[] = {4, 16, 40};     // neurons per lane the kernel is compiled for (40: d = ndec = 1)
+// Entries of a wavefront's list: {type | kResBar | kResPut, first item, a, b}.
+//   RES_SIMPLE, RES_SUM4, RES_INC, RES_DOT: `a` items from the first one on
+//   RES_ENS: slots a .. b - 1; RES_TREE: b units from unit a on
+// kResBar: a barrier follows; kResPut: the next step's feed rows go to LDS before it.
+enum ResType : int32_t { RES_NONE = 0, RES_SIMPLE, RES_SUM4, RES_INC, RES_DOT, RES_ENS, RES_TREE };
+constexpr int32_t kResBar = 16, kResPut = 32;
+// Items (4 words):
+//   SIMPLE {d, src | flags, f2, f3}: d = fma(f2, src, f3) with kResInit, fma(f2,
+//     src, d) without; with kResLowpass d = fma(f2, d, f3 src)
+//   SUM4 {d, s0 | s1 << 16, s2 | s3 << 16, 0}: d = (((0 + s0) + s1) + s2) + s3
+//   INC {d, first entry, entries | kResInit, f3}: from f3 or d, fma(factor, src, .)
+//   DOT {d | kResInit, x, n, weights}: n columns of a row, a part of its sum; its
+//     parts are consecutive items and added in order; b of the entry: M | parts << 24
+// A src with kResFeed is a row of the step's feed.
+constexpr int32_t kResFeed = 1 << 28, kResLowpass = 1 << 29, kResInit = 1 << 30;
+struct ResProgram {
+  bool ok = false;
+  std::string why;
+  int32_t d = 1, ndec = 1, slots = 0, waves = 1, split_sums = 0, multi = 0, spikes = 0;   // multi: an ensemble takes several slots
+  int32_t probe_barrier = 0, sched_len = 0;       // spikes: some outputs are stored
+  float tau_rc = 0, tau_ref = 0, amp = 0;
+  int64_t lds = 0;                                // bytes
+  std::vector<int32_t> row_of;                    // per place: state row (-1: a constant)
+  std::vector<int32_t> sched, sched_n;            // per wavefront 64 entries of 4 words; entries used
+  std::vector<std::array<int32_t, 4>> items;
+  std::vector<int32_t> entries;                   // {place, factor bits} pairs
+  std::vector<int32_t> units;                     // RES_TREE: 4 words {d | rows << 20 | init << 28, x, K, weights}
+  std::vector<int32_t> slot_rec;                  // per (wavefront, slot) 8 words: x, d, s, n, flags, V, ref, 0
+  std::vector<float> slot_par, slot_dec;          // per (wavefront, slot): [d + 1][64] and [ndec][64]
+  std::vector<float> weights;
+  std::vector<int32_t> probe_at;
+};
+// graph_order: sums are taken in the launch drivers' order (the model would run
+// on them), otherwise in k_persistent's.
+ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph_order);
 
 std::unique_ptr<Plan> make_plan(const Model& m, double dt, const PlanOpts& o);
 std::string plan_to_json(const Plan& p);
