@@ -1157,13 +1157,6 @@ __global__ void k_init_rows(float* st, Strides S, int32_t B, int64_t row0, int64
   st[at(S, row0 + r, b)] = vals[r];
 }
 
-__global__ void k_set_ctr(int64_t* ctr, int64_t c0, int64_t c1) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    ctr[0] = c0;
-    ctr[1] = c1;
-  }
-}
-
 // count of non-finite values among x[0..n) (grid-stride; one atomic per workgroup)
 __global__ void __launch_bounds__(256) k_count_nonfinite(const float* x, int64_t n, unsigned int* count) {
   __shared__ unsigned int c;

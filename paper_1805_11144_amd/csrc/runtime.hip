@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -882,6 +883,9 @@ void check_feed(ms_sim* s, const ms_feed& f, size_t elems) {
                            " non-finite values (NaN or Inf)");
 }
 
+// Drivers whose kernels count the steps on the device (s->ctr).
+bool launch_driver(const ms_sim* s) { return s->driver == MS_DRIVER_GRAPH || s->driver == MS_DRIVER_STEPS; }
+
 void stage_feeds(ms_sim* s, int64_t n_steps, const ms_feed* feeds, int32_t n_feeds) {
   const IR& ir = s->plan->ir;
   const int32_t B = s->B;
@@ -893,7 +897,16 @@ void stage_feeds(ms_sim* s, int64_t n_steps, const ms_feed* feeds, int32_t n_fee
       if (f.node_id < 0 || f.node_id >= (int32_t)ir.node_size.size() || !f.data) continue;   // refused below
       check_feed(s, f, (size_t)B * n_steps * ir.node_size[f.node_id]);
     }
-  HIPCHECK(hipMemsetAsync(s->feed_stage, 0, (size_t)n_steps * fr * B * 4, s->stream));
+  // rows without a feed are zero; where every row has one there is nothing to clear
+  std::vector<char> fed(ir.feed_row_of_node.size(), 0);
+  int64_t rows = 0;
+  for (int32_t i = 0; i < n_feeds; ++i) {
+    const int32_t node = feeds[i].node_id;
+    if (node < 0 || node >= (int32_t)fed.size() || ir.feed_row_of_node[node] < 0 || fed[node]) continue;
+    fed[node] = 1;
+    rows += ir.node_size[node];
+  }
+  if (rows < fr) HIPCHECK(hipMemsetAsync(s->feed_stage, 0, (size_t)n_steps * fr * B * 4, s->stream));
   for (int32_t i = 0; i < n_feeds; ++i) {
     const ms_feed& f = feeds[i];
     if (f.node_id < 0 || f.node_id >= (int32_t)ir.feed_row_of_node.size() || ir.feed_row_of_node[f.node_id] < 0)
@@ -1562,7 +1575,6 @@ void run_window(ms_sim* s, int64_t n_steps) {
       hipLaunchKernelGGL(k_w_carry, dim3(grid_items((double)w.rows_v * s->B)), dim3(kBlock), 0, s->stream, v,
                          w.rows_v);
   }
-  hipLaunchKernelGGL(k_set_ctr, dim3(1), dim3(64), 0, s->stream, s->ctr, s->steps_total + n_steps, n_steps);
 }
 
 }  // namespace
@@ -1733,7 +1745,7 @@ ms_status ms_sim_run_steps(ms_sim* s, int64_t n_steps, const ms_feed* feeds, int
     DeviceGuard dg(s->device);
     ensure_capacity(s, n_steps);
     stage_feeds(s, n_steps, feeds, n_feeds);
-    HIPCHECK(hipMemsetAsync(s->ctr + 1, 0, sizeof(int64_t), s->stream));
+    if (launch_driver(s)) HIPCHECK(hipMemsetAsync(s->ctr + 1, 0, sizeof(int64_t), s->stream));
     s->tn = 0;
     HIPCHECK(hipEventRecord(s->ev0, s->stream));
     if (s->resident && !s->res_off) {
@@ -1947,11 +1959,12 @@ ms_status ms_sim_probe_read_bits(ms_sim* s, int32_t probe, uint32_t* out, int64_
 
 // The initial state (ms_sim_reset), queued on the simulator's stream.
 static void reset_state(ms_sim* s) {
-  HIPCHECK(hipMemsetAsync(s->state, 0, std::max<size_t>(1, s->state_rows) * s->B * 4, s->stream));
+  if (s->driver != MS_DRIVER_WINDOW)   // which keeps its state in va and pa
+    HIPCHECK(hipMemsetAsync(s->state, 0, std::max<size_t>(1, s->state_rows) * s->B * 4, s->stream));
   if (s->va)   // block 0 (the carried state); the other blocks are written before they are read
     HIPCHECK(hipMemset2DAsync(s->va, s->vs * 4, 0, (size_t)s->B * 4, std::max<int64_t>(1, s->wplan->rows_v), s->stream));
   if (s->pa) HIPCHECK(hipMemsetAsync(s->pa, 0, (size_t)std::max<int64_t>(1, s->wplan->rows_p) * s->B * 4, s->stream));
-  HIPCHECK(hipMemsetAsync(s->ctr, 0, 2 * sizeof(int64_t), s->stream));
+  if (launch_driver(s)) HIPCHECK(hipMemsetAsync(s->ctr, 0, 2 * sizeof(int64_t), s->stream));
   init_state(s);
   s->steps_total = 0;
   s->res_off = false;
