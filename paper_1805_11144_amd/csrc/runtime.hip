@@ -1100,7 +1100,6 @@ void setup_persistent(ms_sim* s) {
 }
 
 void run_persistent(ms_sim* s, int64_t n_steps) {
-  if (!s->prog.groups) setup_persistent(s);
   s->res_off = false;   // after a step every voltage is at most 1
   const int64_t rows = (int64_t)std::max<size_t>(1, s->state_rows);
   const int threads = s->persistent_threads;
@@ -2065,6 +2064,11 @@ ms_status ms_sim_set_state(ms_sim* s, int32_t which, int32_t id, const float* in
     // k_resident's neuron update holds for trajectories from V <= 1
     if (which == MS_STATE_VOLTAGE)
       for (int64_t k = 0; k < n_elems; ++k) s->res_off |= in[k] > 1.0f;
+    // (its allocations belong here and not in the run, which a caller may capture)
+    if (s->resident && s->res_off && !s->prog.groups) {
+      DeviceGuard dg(s->device);
+      setup_persistent(s);
+    }
   });
 }
 
