@@ -362,7 +362,7 @@ def measure_roofline(M, model, w, sim, info, feeds, bf16=False, plan_opts=None, 
         b = compulsory_bytes_per_step(w) * T
         ach = b / (ms * 1e-3) / 1e9
         return {"bound": "hbm", "achieved": round(ach, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_persistent",
+                "frac": round(ach / HBM_PEAK_GBS, 4), "traffic": None, "kernel": "k_resident or k_persistent",
                 "launch_ms": round(ms, 4), "launches": 1, "work_per_launch": int(b)}
     tsim = sim if drv in (M.DRIVER_WINDOW, M.DRIVER_STEPS) else \
         M.Simulator(model, minibatch=w.minibatch, driver=M.DRIVER_STEPS, probe_capacity_steps=T,
