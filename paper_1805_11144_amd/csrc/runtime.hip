@@ -999,7 +999,7 @@ const void* resident_kernel(const ms_sim* s) {
          : S == 16 ? (const void*)k_resident<1, 1, 16, false> : (const void*)k_resident<1, 1, 40, false>;
 }
 
-void setup_resident(ms_sim* s, const ResProgram& R) {
+void setup_resident(ms_sim* s, const ResProgram& R, int lds_max) {
   ResArgs& A = s->res;
   A.row_of = upload(s, R.row_of);
   A.sched = upload(s, R.sched);
@@ -1031,8 +1031,9 @@ void setup_resident(ms_sim* s, const ResProgram& R) {
   s->res_slots = R.slots;
   s->res_lds = (size_t)R.lds;
   s->resident = true;
+  // the device's limit, not this model's size: simulators share the kernel
   if (s->res_lds > 65536)
-    HIPCHECK(hipFuncSetAttribute(resident_kernel(s), hipFuncAttributeMaxDynamicSharedMemorySize, (int)s->res_lds));
+    HIPCHECK(hipFuncSetAttribute(resident_kernel(s), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
 }
 
 void run_resident(ms_sim* s, int64_t n_steps) {
@@ -1708,7 +1709,7 @@ ms_status ms_sim_create(const ms_model* model, const ms_sim_opts* opts, ms_sim**
       }
       (void)scratch_on(s->device);   // the static staging array's address on this device
       setup_device(s);
-      if (s->driver == MS_DRIVER_PERSISTENT && res.ok) setup_resident(s, res);
+      if (s->driver == MS_DRIVER_PERSISTENT && res.ok) setup_resident(s, res, lds_max);
       else if (s->driver == MS_DRIVER_PERSISTENT) setup_persistent(s);
       if (s->driver == MS_DRIVER_WINDOW) setup_window(s);
       ensure_capacity(s, std::max<int64_t>(1, o->probe_capacity_steps));
