@@ -268,6 +268,9 @@ __global__ void __launch_bounds__(512) k_resident(float* state, int64_t rows, in
             const int32_t at = kHeld ? oat[kHeld ? s0 / NB : 0] : myrec[8 * s + 1];
             if (!PLAIN && A.split) {   // a sum per chunk; the last chunk adds them in order
               mypart[s * ND + q] = t;
+              // other lanes read it: the fence keeps the order of store and loads,
+              // which are at different addresses for every single lane
+              __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
               const int32_t c = fl >> 12;
               if (c > 0 && (fl & 2)) {
                 t = mypart[(s - c) * ND + q];

@@ -81,7 +81,9 @@ def test_order_of_the_persistent_kernel(ns, d, n_feed, K, minibatch):
 
 @pytest.mark.parametrize("ns,fill,d,n_feed,K,minibatch", [
     ((64, 1, 63), 90, 1, 5, 64, 1), ((65, 256), 100, 1, 300, 70, 4), ((65, 64), 300, 1, 7, 128, 2), ((64,), 310, 1, 7, 120, 1),
-    ((130, 200), 85, 2, 30, 127, 3), ((50,), 90, 2, 600, 63, 5)])
+    ((130, 200), 85, 2, 30, 127, 3), ((50,), 90, 2, 600, 63, 5),
+    # two decoded sums over up to four chunks, exchanged between lanes, at every place in a block of eight slots
+    ((256, 193, 255, 129, 256), 75, 2, 3, 64, 2)])
 def test_order_of_the_launch_drivers(ns, fill, d, n_feed, K, minibatch):
     w = recurrent(ns, d, minibatch, n_feed, K, fill=fill)
     same(run(w, [1, 2, 37], 3), run(w, [40], 3, driver=M.DRIVER_STEPS))
