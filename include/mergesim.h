@@ -489,7 +489,11 @@ ms_status ms_sim_train_step(ms_sim* sim, int64_t n_steps, const ms_feed* feeds, 
 ms_status ms_sim_train_param(ms_sim* sim, int32_t which, int32_t id, int32_t function, int32_t gradient,
                              float* out, int64_t cap, int64_t* n_out);
 /* Overwrite a trained parameter (checkpoint restore; n must equal its element
- * count).  Later runs and training steps use the new values. */
+ * count).  Later runs and training steps use the new values, on every driver.
+ * Where planning made a parameter an operator's constant, the planned value
+ * stays: with simplify != 0 a scalar transform of 1 and the biases of ensembles
+ * that are not fused, with MS_FUSE_SYNAPSES on the launch drivers the scalar
+ * transforms of the connections it fuses. */
 ms_status ms_sim_set_train_param(ms_sim* sim, int32_t which, int32_t id, int32_t function, const float* in,
                                  int64_t n);
 

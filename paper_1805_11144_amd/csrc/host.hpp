@@ -383,8 +383,10 @@ struct ResProgram {
   std::vector<int32_t> probe_at;
 };
 // graph_order: sums are taken in the launch drivers' order (the model would run
-// on them), otherwise in k_persistent's.
-ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph_order);
+// on them), otherwise in k_persistent's.  params: the parameter bases as they
+// are now (null: as planned); the tables' sizes do not depend on their values.
+ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph_order,
+                         const std::vector<std::vector<float>>* params = nullptr);
 
 std::unique_ptr<Plan> make_plan(const Model& m, double dt, const PlanOpts& o);
 std::string plan_to_json(const Plan& p);

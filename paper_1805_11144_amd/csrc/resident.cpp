@@ -203,7 +203,8 @@ struct Prep {
 
 }  // namespace
 
-ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph_order) {
+ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph_order,
+                         const std::vector<std::vector<float>>* params) {
   ResProgram R;
   auto no = [&](const char* why) { R.why = why; return R; };
   const IR& ir = p.ir;
@@ -214,6 +215,7 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
   if (nrows == 0) return no("no batched signals");
   std::vector<std::vector<float>> base(ir.bases.size());
   auto param = [&](int32_t b) -> const std::vector<float>& {
+    if (params) return (*params)[(size_t)b];
     std::vector<float>& v = base[(size_t)b];
     if (v.empty()) {
       v.assign((size_t)std::max<int64_t>(1, p.base_rows[b] * ir.bases[b].cols), 0.0f);
@@ -375,7 +377,8 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
                                      : bt                  ? 1.0f
                                                            : param(g.src.base)[(size_t)row_at(g.src, e)]);
               en.push_back({bt ? src_at(row_at(g.src, e)) : 0, f});
-              adds = adds && f == bits(1.0f) && !(en.back().first & kResFeed);
+              // by type and not by the factor's value, which may be set later
+              adds = adds && bt && g.type == OP_COPY_INC && !(en.back().first & kResFeed);
             }
             if (en.size() == 1) {
               simple.push_back({d, en[0].first | (gi.init ? kResInit : 0), en[0].second, start});

@@ -13,11 +13,13 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -175,7 +177,7 @@ struct ms_sim {
   ResArgs res{};
   bool res_plain = false;
   int32_t res_d = 1, res_slots = 0;
-  size_t res_lds = 0;
+  size_t res_lds = 0, res_nweight = 0;
   std::vector<void*> extra_allocs;   // transposed weights and their offsets, extra pools
   // window driver
   std::unique_ptr<WindowPlan> wplan;
@@ -196,6 +198,9 @@ struct ms_sim {
   hipStream_t side[kSide] = {};
   hipEvent_t side_ev[kSide + 1] = {};
   std::vector<std::vector<float>> host_bases;   // host copies of parameter bases
+  // per device copy of parameters: made again from host_bases where elements
+  // lo .. hi - 1 of base b have changed (b < 0: the whole copy)
+  std::vector<std::function<void(int32_t b, int64_t lo, int64_t hi)>> remake;
   float* init_vals = nullptr;        // initial values of batched state signals that have one
   std::vector<std::pair<int32_t, int64_t>> init_sigs;   // (signal, offset in init_vals)
   float* pes_part = nullptr;         // partial decodes of the learned-decoder launches
@@ -307,6 +312,32 @@ struct PoolBuilder {
 };
 
 const std::vector<float>& host_param_base(ms_sim* s, int32_t base);
+
+// A device copy of parameters in another form, made from host_bases block by
+// block and made again where the parameters are set later: elements s0 ..
+// s0 + n - 1 of base `base` become elements d0 .. d0 + dn - 1 of dev by
+// fill(block, its index, its source elements, its place in zeroed memory).
+struct CopyBlock { int32_t base; int64_t s0, n, d0, dn; };
+
+template <class T, class Fill>
+void add_copy(ms_sim* s, T* dev, std::vector<CopyBlock> blks, Fill fill) {
+  s->remake.push_back([s, dev, blks = std::move(blks), fill](int32_t base, int64_t lo, int64_t hi) {
+    int64_t d0 = INT64_MAX, d1 = 0;   // one copy spans every block that changed
+    for (const CopyBlock& c : blks)
+      if (base < 0 || (c.base == base && c.s0 < hi && c.s0 + c.n > lo)) {
+        d0 = std::min(d0, c.d0);
+        d1 = std::max(d1, c.d0 + c.dn);
+      }
+    if (d1 <= d0) return;
+    std::vector<T> t((size_t)(d1 - d0), T(0));
+    for (size_t i = 0; i < blks.size(); ++i) {
+      const CopyBlock& c = blks[i];
+      if (c.d0 >= d0 && c.d0 + c.dn <= d1) fill(c, i, host_param_base(s, c.base).data() + c.s0, t.data() + (c.d0 - d0));
+    }
+    HIPCHECK(hipMemcpy(dev + d0, t.data(), t.size() * sizeof(T), hipMemcpyHostToDevice));
+  });
+  s->remake.back()(-1, 0, 0);
+}
 
 // Lowered groups -> launch records (index and parameter arrays uploaded into
 // pools owned by the simulator); `extra_ints` is uploaded alongside and its
@@ -458,19 +489,20 @@ void build_launches(ms_sim* s, const std::vector<LGroup>& groups, std::vector<La
       E.enc = g.a.base >= 0 ? s->base_ptr[g.a.base] : nullptr;
       if (g.a.base >= 0 && g.ens_d > 0 && s->B < 32) {
         // per-op transposed encoder blocks for the lanes-over-neurons kernel
-        const std::vector<float>& he = host_param_base(s, g.a.base);
-        std::vector<float> t(he.size(), 0.0f);
-        const int64_t d = g.ens_d;
-        for (size_t k = 0; k < g.ens_n.size(); ++k) {
-          if (g.ens_x[k] < 0 || g.ens_enc[k] < 0) continue;   // no input, no encoders
-          const int64_t e0 = g.ens_enc[k], n = g.ens_n[k];
-          for (int64_t r = 0; r < n; ++r)
-            for (int64_t q = 0; q < d; ++q) t[(size_t)(e0 * d + q * n + r)] = he[(size_t)((e0 + r) * d + q)];
-        }
-        float* dt_ = dev_alloc<float>(std::max<size_t>(1, t.size()));
-        HIPCHECK(hipMemcpy(dt_, t.data(), t.size() * 4, hipMemcpyHostToDevice));
+        float* dt_ = dev_alloc<float>(std::max<size_t>(1, host_param_base(s, g.a.base).size()));
         s->extra_allocs.push_back(dt_);
         E.encT = dt_;
+        std::vector<CopyBlock> blks;
+        for (size_t k = 0; k < g.ens_n.size(); ++k) {
+          if (g.ens_x[k] < 0 || g.ens_enc[k] < 0) continue;   // no input, no encoders
+          const int64_t e0 = (int64_t)g.ens_enc[k] * g.ens_d, n = (int64_t)g.ens_n[k] * g.ens_d;
+          blks.push_back({g.a.base, e0, n, e0, n});
+        }
+        add_copy(s, dt_, std::move(blks), [d = (int64_t)g.ens_d](const CopyBlock& c, size_t, const float* he, float* t) {
+          const int64_t n = c.n / d;
+          for (int64_t r = 0; r < n; ++r)
+            for (int64_t q = 0; q < d; ++q) t[q * n + r] = he[r * d + q];
+        });
       }
       if (s->decode == MS_DECODE_EVENT && g.ens_type == 0 && E.ndec > 0 && s->B < 32 &&
           (s->driver == MS_DRIVER_STEPS || s->driver == MS_DRIVER_GRAPH)) {
@@ -480,19 +512,23 @@ void build_launches(ms_sim* s, const std::vector<LGroup>& groups, std::vector<La
         const int64_t row = dec_bucket(E.ndec);
         int64_t nmax = 1;
         for (int32_t n : g.ens_n) nmax = std::max<int64_t>(nmax, n);
-        std::vector<float> t((size_t)(g.ens_n.size() * nmax * row), 0.0f);
-        for (int f = 0, q0 = 0; f < E.nf; q0 += E.df[f], ++f) {
-          const std::vector<float>& hd = host_param_base(s, g.ens_Dbase[f]);
-          const int64_t cols = E.Dcols[f];
-          for (size_t k = 0; k < g.ens_n.size(); ++k)
-            for (int32_t q = 0; q < E.df[f]; ++q)
-              for (int64_t r = 0; r < g.ens_n[k]; ++r)
-                t[(size_t)(((int64_t)k * nmax + r) * row + q0 + q)] =
-                    hd[(size_t)(((int64_t)g.ens_D[f][k] + q) * cols + r)];
-        }
-        float* dd = dev_alloc<float>(t.size());
-        HIPCHECK(hipMemcpy(dd, t.data(), t.size() * 4, hipMemcpyHostToDevice));
+        const size_t len = g.ens_n.size() * (size_t)(nmax * row);
+        float* dd = dev_alloc<float>(len);
         s->extra_allocs.push_back(dd);
+        std::vector<CopyBlock> blks;
+        std::vector<std::array<int32_t, 3>> outs;   // per block: first output, outputs, neurons
+        for (int f = 0, q0 = 0; f < E.nf; q0 += E.df[f], ++f)
+          for (size_t k = 0; k < g.ens_n.size(); ++k) {
+            const int64_t cols = E.Dcols[f];
+            blks.push_back({g.ens_Dbase[f], g.ens_D[f][k] * cols, E.df[f] * cols, (int64_t)k * nmax * row, nmax * row});
+            outs.push_back({q0, E.df[f], g.ens_n[k]});
+          }
+        add_copy(s, dd, std::move(blks), [outs, row](const CopyBlock& c, size_t i, const float* hd, float* t) {
+          const auto& o = outs[i];
+          const int64_t cols = c.n / std::max(1, o[1]);
+          for (int32_t q = 0; q < o[1]; ++q)
+            for (int64_t r = 0; r < o[2]; ++r) t[r * row + o[0] + q] = hd[q * cols + r];
+        });
         E.decT = dd;
         E.dT_op = nmax * row;
         E.dT_row = (int32_t)row;
@@ -1012,6 +1048,24 @@ void setup_resident(ms_sim* s, const ResProgram& R, int lds_max) {
   A.slot_dec = upload(s, R.slot_dec);
   A.weights = upload(s, R.weights);
   A.probe_at = upload(s, R.probe_at);
+  // the tables that hold parameters, made again from the parameters as they are
+  s->remake.push_back([s, lds_max, graph_order = R.split_sums != 0](int32_t, int64_t, int64_t) {
+    const ResProgram N = make_resident(*s->plan, s->B, lds_max, graph_order, &s->host_bases);
+    const ResArgs& a = s->res;
+    const size_t ns = (size_t)N.waves * N.slots * 64;
+    if (!N.ok || (size_t)a.nitem != N.items.size() || (size_t)a.nent != N.entries.size() || s->res_nweight != N.weights.size() ||
+        N.waves != a.waves || N.slots != s->res_slots || N.slot_par.size() != ns * (N.d + 1) || N.slot_dec.size() != ns * N.ndec)
+      fail(MS_E_STATE, "the resident program's tables changed their size");
+    auto again = [](const void* d, const auto& v) {
+      if (!v.empty()) HIPCHECK(hipMemcpy(const_cast<void*>(d), v.data(), v.size() * sizeof(v[0]), hipMemcpyHostToDevice));
+    };
+    again(a.items, N.items);
+    again(a.entries, N.entries);
+    again(a.slot_par, N.slot_par);
+    again(a.slot_dec, N.slot_dec);
+    again(a.weights, N.weights);
+  });
+  s->res_nweight = R.weights.size();
   A.nrow = (int32_t)R.row_of.size();
   A.nunit = (int32_t)R.units.size() / 4;
   A.nitem = (int32_t)R.items.size();
@@ -1056,26 +1110,21 @@ void setup_persistent(ms_sim* s) {
     if (l.type == OP_DOT_INC) {
       // transposed copy of every op's [M][K] block, [K][M], in one buffer
       const int64_t blk = (int64_t)l.M * l.K;
-      std::vector<float> wt((size_t)(blk * l.rows));
       std::vector<int64_t> off((size_t)l.rows);
-      std::vector<int32_t> wrow((size_t)l.rows);
-      HIPCHECK(hipMemcpy(wrow.data(), l.w_row, wrow.size() * 4, hipMemcpyDeviceToHost));
-      const LGroup& lg = s->plan->lowered[gi];
-      const std::vector<float>& host_w = host_param_base(s, lg.a.base);
-      const int64_t cols = s->plan->ir.bases[lg.a.base].cols;
-      for (int64_t op = 0; op < l.rows; ++op) {
-        off[op] = op * blk;
-        for (int32_t m = 0; m < l.M; ++m)
-          for (int32_t k = 0; k < l.K; ++k)
-            wt[(size_t)(op * blk + (int64_t)k * l.M + m)] =
-                host_w[(size_t)(((int64_t)wrow[op] + m) * cols + (cols == 1 ? 0 : k)) + (cols == 1 ? k : 0)];
-      }
-      float* dwt = dev_alloc<float>(std::max<size_t>(1, wt.size()));
-      int64_t* doff = dev_alloc<int64_t>(std::max<size_t>(1, off.size()));
-      HIPCHECK(hipMemcpy(dwt, wt.data(), wt.size() * 4, hipMemcpyHostToDevice));
-      HIPCHECK(hipMemcpy(doff, off.data(), off.size() * 8, hipMemcpyHostToDevice));
+      for (int64_t op = 0; op < l.rows; ++op) off[op] = op * blk;
+      float* dwt = dev_alloc<float>(std::max<size_t>(1, (size_t)(blk * l.rows)));
       s->extra_allocs.push_back(dwt);
+      const LGroup& lg = s->plan->lowered[gi];
+      std::vector<CopyBlock> blks;
+      for (int64_t op = 0; op < l.rows; ++op)
+        blks.push_back({lg.a.base, (int64_t)lg.w_row[op] * s->plan->ir.bases[lg.a.base].cols, blk, op * blk, blk});
+      add_copy(s, dwt, std::move(blks), [M = l.M, K = l.K](const CopyBlock&, size_t, const float* w, float* t) {
+        for (int64_t m = 0; m < M; ++m)
+          for (int64_t k = 0; k < K; ++k) t[k * M + m] = w[m * K + k];
+      });
+      int64_t* doff = dev_alloc<int64_t>(std::max<size_t>(1, off.size()));
       s->extra_allocs.push_back(doff);
+      HIPCHECK(hipMemcpy(doff, off.data(), off.size() * 8, hipMemcpyHostToDevice));
       g.wt_base = dwt;
       g.wt_off = doff;
       const int64_t out_rows = l.rows * (int64_t)l.M;
@@ -1353,14 +1402,15 @@ void setup_window(ms_sim* s) {
     if (s->gemm_dtype == MS_GEMM_BF16 && bf16_product(s, l)) {
       // each op's [M][K] block of W, rounded to nearest even, packed op after op
       const LGroup& g = runs[k].g;
-      const std::vector<float>& hw = host_param_base(s, g.a.base);
-      std::vector<uint16_t> w16((size_t)l.rows * l.M * l.K);
-      for (int64_t op = 0; op < l.rows; ++op)
-        for (int64_t e = 0; e < (int64_t)l.M * l.K; ++e)
-          w16[(size_t)(op * l.M * l.K + e)] = bf16_rne(hw[(size_t)((int64_t)g.w_row[op] * l.K + e)]);
-      uint16_t* d = dev_alloc<uint16_t>(w16.size());
+      const size_t blk = (size_t)l.M * l.K;
+      uint16_t* d = dev_alloc<uint16_t>((size_t)l.rows * blk);
       s->extra_allocs.push_back(d);
-      HIPCHECK(hipMemcpy(d, w16.data(), w16.size() * sizeof(uint16_t), hipMemcpyHostToDevice));
+      std::vector<CopyBlock> blks;
+      for (int64_t op = 0; op < l.rows; ++op)
+        blks.push_back({g.a.base, (int64_t)g.w_row[op] * l.K, (int64_t)blk, op * (int64_t)blk, (int64_t)blk});
+      add_copy(s, d, std::move(blks), [](const CopyBlock& c, size_t, const float* w, uint16_t* t) {
+        for (int64_t e = 0; e < c.n; ++e) t[e] = bf16_rne(w[e]);
+      });
       l.w16 = d;
     }
     if (l.rows > 0 && packed_product(l)) {

@@ -471,6 +471,15 @@ ms_status ms_sim_set_train_param(ms_sim* s, int32_t which, int32_t id, int32_t f
     HIPCHECK(hipStreamSynchronize(s->stream));
     HIPCHECK(hipMemcpy(t.p, h.data(), (size_t)n * 4, hipMemcpyHostToDevice));
     s->pack_stale = true;
+    // the other copies made at creation: resident tables, transposed encoders
+    // and products, neuron-major decoders, bf16 weights
+    // (a simulator that can train has none of them)
+    if (!s->remake.empty()) {
+      const int32_t b = s->plan->ir.sigs[t.sig].base;
+      const int64_t lo = t.p - s->base_ptr[b];
+      std::copy(h.begin(), h.end(), s->host_bases[(size_t)b].begin() + lo);
+      for (const auto& f : s->remake) f(b, lo, lo + n);
+    }
   });
 }
 
