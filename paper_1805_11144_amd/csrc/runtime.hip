@@ -173,7 +173,7 @@ struct ms_sim {
   int64_t scratch_n = 0;             // per-column scratch floats of the persistent kernel
   float* col_scratch = nullptr;      // global scratch when state is not LDS-resident
   bool resident = false;             // the step runs as a resident program (k_resident)
-  bool res_off = false;              // the next run takes k_persistent: a voltage above threshold was set
+  bool res_first = false;            // the next step starts from voltages that a caller set
   ResArgs res{};
   bool res_plain = false;
   int32_t res_d = 1, res_slots = 0;
@@ -1025,8 +1025,14 @@ T* upload(ms_sim* s, const std::vector<T>& v) {
   return d;
 }
 
-const void* resident_kernel(const ms_sim* s) {
+// first: for the step after a caller set voltages (one form for plain models too)
+const void* resident_kernel(const ms_sim* s, bool first) {
   const int S = s->res_slots;
+  if (first && s->res_d > 1)
+    return S == 4 ? (const void*)k_resident<2, 2, 4, false, true> : (const void*)k_resident<2, 2, 16, false, true>;
+  if (first)
+    return S == 4 ? (const void*)k_resident<1, 1, 4, false, true>
+           : S == 16 ? (const void*)k_resident<1, 1, 16, false, true> : (const void*)k_resident<1, 1, 40, false, true>;
   if (s->res_d > 1) return S == 4 ? (const void*)k_resident<2, 2, 4, false> : (const void*)k_resident<2, 2, 16, false>;
   if (s->res_plain)
     return S == 4 ? (const void*)k_resident<1, 1, 4, true>
@@ -1087,16 +1093,29 @@ void setup_resident(ms_sim* s, const ResProgram& R, int lds_max) {
   s->resident = true;
   // the device's limit, not this model's size: simulators share the kernel
   if (s->res_lds > 65536)
-    HIPCHECK(hipFuncSetAttribute(resident_kernel(s), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
+    for (const bool first : {false, true})
+      HIPCHECK(hipFuncSetAttribute(resident_kernel(s, first), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
 }
 
+// The step after a caller set voltages is a launch of its own, whose neuron
+// update takes any voltage.  So is the first step of a run that the caller
+// captures: voltages may be set between the replays.
 void run_resident(ms_sim* s, int64_t n_steps) {
   int64_t rows = (int64_t)std::max<size_t>(1, s->state_rows);
   int32_t fr = s->plan->ir.feed_rows;
-  const float* stage = s->feed_stage;
-  void* args[] = {&s->state, &rows, &s->B, &s->res, &n_steps, &s->dt, &stage, &fr, &s->probe_buf, &s->steps_total};
-  HIPCHECK(hipLaunchKernel(resident_kernel(s), dim3((unsigned)s->B), dim3((unsigned)(64 * s->res.waves)), args,
-                           s->res_lds, s->stream));
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  HIPCHECK(hipStreamIsCapturing(s->stream, &cap));
+  auto launch = [&](bool first, int64_t k0, int64_t n) {
+    const float* stage = s->feed_stage + k0 * fr * s->B;
+    int64_t t0 = s->steps_total + k0;
+    void* args[] = {&s->state, &rows, &s->B, &s->res, &n, &s->dt, &stage, &fr, &s->probe_buf, &t0};
+    HIPCHECK(hipLaunchKernel(resident_kernel(s, first), dim3((unsigned)s->B), dim3((unsigned)(64 * s->res.waves)), args,
+                             s->res_lds, s->stream));
+  };
+  const int64_t k = s->res_first || cap != hipStreamCaptureStatusNone ? 1 : 0;
+  if (k) launch(true, 0, 1);
+  if (n_steps > k) launch(false, k, n_steps - k);
+  s->res_first = false;
 }
 
 void setup_persistent(ms_sim* s) {
@@ -1150,7 +1169,6 @@ void setup_persistent(ms_sim* s) {
 }
 
 void run_persistent(ms_sim* s, int64_t n_steps) {
-  s->res_off = false;   // after a step every voltage is at most 1
   const int64_t rows = (int64_t)std::max<size_t>(1, s->state_rows);
   const int threads = s->persistent_threads;
   const size_t lds = (size_t)(rows + s->scratch_n) * sizeof(float);
@@ -1798,7 +1816,7 @@ ms_status ms_sim_run_steps(ms_sim* s, int64_t n_steps, const ms_feed* feeds, int
     if (launch_driver(s)) HIPCHECK(hipMemsetAsync(s->ctr + 1, 0, sizeof(int64_t), s->stream));
     s->tn = 0;
     HIPCHECK(hipEventRecord(s->ev0, s->stream));
-    if (s->resident && !s->res_off) {
+    if (s->resident) {
       run_resident(s, n_steps);
     } else if (s->driver == MS_DRIVER_PERSISTENT) {
       run_persistent(s, n_steps);
@@ -2017,7 +2035,7 @@ static void reset_state(ms_sim* s) {
   if (launch_driver(s)) HIPCHECK(hipMemsetAsync(s->ctr, 0, 2 * sizeof(int64_t), s->stream));
   init_state(s);
   s->steps_total = 0;
-  s->res_off = false;
+  s->res_first = false;
 }
 
 ms_status ms_sim_reset(ms_sim* s) {
@@ -2112,14 +2130,8 @@ ms_status ms_sim_set_state(ms_sim* s, int32_t which, int32_t id, const float* in
     const int32_t sig = state_signal(s, which, id);
     if (n_elems != (int64_t)s->plan->ir.sigs[sig].rows * s->B) fail(MS_E_INVALID, "state size mismatch");
     state_copy(s, sig, const_cast<float*>(in), true);
-    // k_resident's neuron update holds for trajectories from V <= 1
-    if (which == MS_STATE_VOLTAGE)
-      for (int64_t k = 0; k < n_elems; ++k) s->res_off |= in[k] > 1.0f;
-    // (its allocations belong here and not in the run, which a caller may capture)
-    if (s->resident && s->res_off && !s->prog.groups) {
-      DeviceGuard dg(s->device);
-      setup_persistent(s);
-    }
+    if (which == MS_STATE_VOLTAGE)   // k_resident's usual neuron update starts from V <= 1
+      for (int64_t k = 0; k < n_elems; ++k) s->res_first |= in[k] > 1.0f;
   });
 }
 
