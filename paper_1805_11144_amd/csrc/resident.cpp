@@ -268,6 +268,9 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
   if (graph_order && (B >= 8 || tree > 16 * kResWaves || dot > 64 * kResWaves)) return no("products too large for one workgroup");
   if (!((float)p.dt * (float)(1.0 / (double)first->tau_rc[0]) <= 0.0625f)) return no("a step past tau_rc / 16");
   if (R.d > 1 || R.ndec > 1) R.d = kResD, R.ndec = kResDec;   // the two forms the kernel is compiled for
+  // (found out before any table is built; by wavefront, it is checked once the
+  // ensembles have theirs)
+  if (slots > (int64_t)kResWaves * (R.d == 1 ? kResSlots[2] : kResSlots[1])) return no("more neurons than the wavefronts' registers hold");
   R.tau_rc = first->tau_rc[0]; R.tau_ref = first->tau_ref[0]; R.amp = first->amp[0];
   R.waves = (int32_t)std::min<int64_t>(kResWaves, std::max<int64_t>(1, (slots + 3) / 4));   // about four slots each
   if (ir.feed_rows > 2 * 64 * R.waves) return no("more feed rows than the workgroup fetches ahead");

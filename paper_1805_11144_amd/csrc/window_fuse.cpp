@@ -14,6 +14,7 @@
 // Each row's value is formed by the same operations in the same order, so the
 // results are the same (a copied -0 may become +0 and back).
 #include <algorithm>
+#include <iterator>
 
 #include "host.hpp"
 
@@ -35,12 +36,33 @@ LOperand operand_of(int32_t base, std::vector<int32_t> rows) {
 
 int64_t entries(const LGroup& g) { return g.ptr.empty() ? g.rows : (int64_t)g.ptr.back(); }
 
+// The phases that write or read a row, in order.  There are a few for each of
+// thousands of rows, so up to three are held without an allocation.
+struct Phases {
+  int32_t n = 0, in[3];
+  std::vector<int32_t> more;   // all of them when there are more than three
+  const int32_t* begin() const { return n <= 3 ? in : more.data(); }
+  const int32_t* end() const { return begin() + n; }
+  size_t size() const { return (size_t)n; }
+  int32_t operator[](size_t k) const { return begin()[k]; }
+  bool ends_with(int32_t k) const { return n > 0 && begin()[n - 1] == k; }
+  void push_back(int32_t k) {
+    if (n < 3) in[n] = k;
+    else if (n == 3) more.assign(in, in + 3);
+    if (n >= 3) more.push_back(k);
+    ++n;
+  }
+  void assign(const std::vector<int32_t>& v) {
+    n = 0;
+    for (int32_t k : v) push_back(k);
+  }
+};
+
 struct Fuser {
   const Plan& p;
   const WindowPlan& w;
   std::vector<WRun>& run;
-  std::vector<std::vector<int32_t>> writers;   // per versioned row: phases that write it, in order
-  std::vector<std::vector<int32_t>> readers;   // per versioned row: phases that read it
+  std::vector<Phases> writers, readers;   // per versioned row
   std::vector<char> probed;
 
   bool batched(const LOperand& o) const { return o.base >= 0 && p.ir.bases[o.base].cls == SC_BATCHED; }
@@ -94,19 +116,20 @@ struct Fuser {
   }
 
   void index() {
-    writers.assign((size_t)w.rows_v, {});
-    readers.assign((size_t)w.rows_v, {});
+    writers.resize((size_t)w.rows_v);
+    readers.resize((size_t)w.rows_v);
+    for (Phases& v : writers) v.n = 0;
+    for (Phases& v : readers) v.n = 0;
     for (int32_t k = 0; k < (int32_t)run.size(); ++k) {
       if (run[k].skip) continue;
-      each_write(k, [&](int64_t r) { if (writers[r].empty() || writers[r].back() != k) writers[r].push_back(k); });
-      each_read(k, [&](int64_t r) { if (readers[r].empty() || readers[r].back() != k) readers[r].push_back(k); });
+      each_write(k, [&](int64_t r) { if (!writers[r].ends_with(k)) writers[r].push_back(k); });
+      each_read(k, [&](int64_t r) { if (!readers[r].ends_with(k)) readers[r].push_back(k); });
     }
   }
 
   // Increments that are the first writer after a reset or a parameter copy.
   void start_increments() {
     const int32_t n = (int32_t)run.size();
-    std::vector<std::vector<int64_t>> pos((size_t)n);   // per RESET / COPY phase: position of each row
     std::vector<int64_t> where((size_t)w.rows_v, -1);   // row -> position in its first writer
     for (int32_t k = 0; k < n; ++k)
       if (run[k].g.type == OP_RESET || run[k].g.type == OP_COPY)
@@ -121,7 +144,7 @@ struct Fuser {
       each_write(k, [&](int64_t r) {
         if (!ok) return;
         rows.push_back(r);
-        const std::vector<int32_t>& ws = writers[r];
+        const Phases& ws = writers[r];
         if (ws.size() < 2 || ws[1] != k || (src >= 0 && ws[0] != src)) { ok = false; return; }
         src = ws[0];
         const LGroup& f = run[src].g;
@@ -247,21 +270,24 @@ struct Fuser {
     for (size_t k = 0; k < p.ir.sigs.size(); ++k)
       if (p.ir.sigs[k].cls == SC_BATCHED && p.ir.sigs[k].state && !w.priv[k])
         for (int32_t r = 0; r < p.ir.sigs[k].rows; ++r) state[(size_t)(w.sig_row[k] + r)] = 1;
+    std::vector<std::pair<int32_t, int32_t>> alias((size_t)w.rows_v, {-1, 1});
     for (int32_t k = 0; k < (int32_t)run.size(); ++k) {
       const LGroup& g = run[k].g;
       if (run[k].skip || !batched(g.src)) continue;
       if (!(g.type == OP_COPY || (g.type == OP_COPY_INC && run[k].init == 1 && run[k].init_vals.empty() && entries(g) == g.rows)))
         continue;
-      std::vector<std::pair<int32_t, int32_t>> alias((size_t)w.rows_v, {-1, 1});
       bool ok = true;
-      std::vector<int32_t> rd;
       for (int64_t r = 0; r < g.rows && ok; ++r) {
         const int64_t d = row_at(g.dst, r);
         ok = writers[d].size() == 1 && !probed[d] && !state[d];
+      }
+      if (!ok) continue;
+      std::vector<int32_t> rd;
+      for (int64_t r = 0; r < g.rows; ++r) {
+        const int64_t d = row_at(g.dst, r);
         alias[d] = {(int32_t)row_at(g.src, r), run[k].src_blk};
         rd.insert(rd.end(), readers[d].begin(), readers[d].end());
       }
-      if (!ok) continue;
       std::sort(rd.begin(), rd.end());
       rd.erase(std::unique(rd.begin(), rd.end()), rd.end());
       std::vector<WRun> saved;
@@ -270,12 +296,22 @@ struct Fuser {
         saved.push_back(run[rd[done]]);
         ok = rd[done] > k && rewrite(run[rd[done]], alias);
       }
-      if (ok) {
+      if (ok) {   // the sources' readers are now the copies' readers as well, but not phase k
         run[k].skip = true;
-        index();
+        std::vector<int32_t> both;
+        for (int64_t r = 0; r < g.rows; ++r) {
+          const int64_t d = row_at(g.dst, r);
+          Phases& s = readers[row_at(g.src, r)];
+          both.clear();
+          std::set_union(s.begin(), s.end(), readers[d].begin(), readers[d].end(), std::back_inserter(both));
+          both.erase(std::remove(both.begin(), both.end(), k), both.end());
+          s.assign(both);
+          readers[d].n = writers[d].n = 0;
+        }
       } else {
         for (size_t i = 0; i < saved.size(); ++i) run[rd[i]] = saved[i];
       }
+      for (int64_t r = 0; r < g.rows; ++r) alias[row_at(g.dst, r)] = {-1, 1};
     }
   }
 
@@ -318,7 +354,7 @@ struct Fuser {
       q.jx_blk = e.src_blk;
       e.skip = true;
       // the filter that x is
-      const std::vector<int32_t>& wx = writers[x[0]];
+      const Phases& wx = writers[x[0]];
       if (keep || q.g.type != OP_LIF || e.src_blk != 0 || wx.size() != 1 || run[wx[0]].g.type != OP_LOWPASS) continue;
       const int32_t pl = wx[0];
       WRun& f = run[pl];
