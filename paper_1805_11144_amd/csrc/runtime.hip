@@ -1720,6 +1720,9 @@ static void init_state(ms_sim* s) {
 
 extern "C" {
 
+// Whether a phase or group is launched: the window driver folds some into others.
+static bool launched(const ms_sim* s, const Launch& l) { return s->driver != MS_DRIVER_WINDOW || (!l.skip && l.rows > 0); }
+
 // MS_LOG (any value but "0"): the plan summary on stderr when a simulator is
 // created: the driver, the merged groups it launches per step (per window for
 // the window driver) with their sizes and kernels' shapes, and the bytes of
@@ -1736,10 +1739,12 @@ static void log_sim(const ms_sim* s) {
     (p.ir.bases[b].cls == SC_BATCHED ? state_b : param_b) += p.base_rows[b] * p.ir.bases[b].cols * 4;
   std::fprintf(stderr, "mergesim: driver %s, minibatch %d, %zu signals, %zu operators in %zu merged groups; "
                "%zu launches per %s; state %lld B per batch column, parameters %lld B\n",
-               dn[s->driver], s->B, p.ir.sigs.size(), p.ir.ops.size(), p.groups.size(), ls.size(),
+               dn[s->driver], s->B, p.ir.sigs.size(), p.ir.ops.size(), p.groups.size(),
+               (size_t)std::count_if(ls.begin(), ls.end(), [s](const Launch& l) { return launched(s, l); }),
                win ? "window" : "step", (long long)state_b, (long long)param_b);
   for (size_t k = 0; k < ls.size(); ++k) {
     const Launch& l = ls[k];
+    if (!launched(s, l)) continue;
     std::fprintf(stderr, "mergesim:   %2zu %-16s rows %lld", k, op_type_name(l.type), (long long)l.rows);
     if (l.type == OP_DOT_INC) std::fprintf(stderr, ", W %d x %d", l.M, l.K);
     if (l.type == OP_ENS)
@@ -1954,7 +1959,9 @@ ms_status ms_sim_info(const ms_sim* s, int32_t* driver_out, int32_t* groups_out)
   return guarded([&] {
     if (!s) fail(MS_E_INVALID, "NULL sim");
     if (driver_out) *driver_out = s->driver;
-    if (groups_out) *groups_out = (int32_t)(s->driver == MS_DRIVER_WINDOW ? s->wl.size() : s->launches.size());
+    const std::vector<Launch>& ls = s->driver == MS_DRIVER_WINDOW ? s->wl : s->launches;
+    if (groups_out)
+      *groups_out = (int32_t)std::count_if(ls.begin(), ls.end(), [s](const Launch& l) { return launched(s, l); });
   });
 }
 

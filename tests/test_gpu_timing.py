@@ -38,3 +38,19 @@ def test_kernel_times_fit_in_the_run(name, kw):
     if name == "pes":
         ms, n = times[MS.OP_PES_DECODE_UPDATE]
         assert n == w.n_steps and ms > 0
+
+
+@pytest.mark.parametrize("name,kw", [
+    ("c2", dict(n_steps=20, minibatch=4, D=8, n_neurons=20, n_eval=100)),
+    ("c3", dict(n_steps=20, minibatch=8, n_in=20, n_hidden=72, n_out=4)),
+    ("c4", dict(n_steps=20, minibatch=4, n_ens=5, n_neurons=40, dims=4, n_eval=60)),
+])
+def test_launches_per_window(name, kw):
+    """What a simulator on the window driver says it launches in a window is
+    what it launches: phases folded into others are not counted."""
+    w = make_workload(name, **kw)
+    with M.Simulator(M.model_from_spec(w.spec), minibatch=w.minibatch, driver=M.DRIVER_WINDOW,
+                     probe_capacity_steps=w.n_steps) as sim:
+        sim.set_timing(True)
+        sim.run_steps(w.n_steps, w.feeds)
+        assert sim.info()["groups_per_step"] == sum(sim.kernel_time(t)[1] for t in range(14))
