@@ -369,7 +369,7 @@ struct ResProgram {
   bool ok = false;
   std::string why;
   int32_t d = 1, ndec = 1, slots = 0, waves = 1, split_sums = 0, multi = 0, spikes = 0;   // multi: an ensemble takes several slots
-  int32_t probe_barrier = 0, sched_len = 0;       // spikes: some outputs are stored
+  int32_t probe_barrier = 0;                      // spikes: some outputs are stored
   float tau_rc = 0, tau_ref = 0, amp = 0;
   int64_t lds = 0;                                // bytes
   std::vector<int32_t> row_of;                    // per place: state row (-1: a constant)

@@ -510,7 +510,6 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
   // a wavefront's list sits in its lanes: entry i in lane i, one more past the end
   for (auto& w : sched) {
     if (w.size() > 63) return no("more entries a step than lanes");
-    R.sched_len = std::max(R.sched_len, (int32_t)w.size());
   }
   for (auto& w : sched) {
     const size_t n = w.size();

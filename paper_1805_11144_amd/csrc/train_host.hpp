@@ -367,7 +367,6 @@ ms_status ms_sim_train_step(ms_sim* s, int64_t n_steps, const ms_feed* feeds, in
       s->loss_part = dev_alloc<float>(nparts);
       s->loss_part_n = nparts;
     }
-    HIPCHECK(hipMemsetAsync(s->ctr + 1, 0, sizeof(int64_t), s->stream));
     s->tn = 0;
     HIPCHECK(hipEventRecord(s->ev0, s->stream));
     run_window(s, n_steps);
