@@ -345,6 +345,7 @@ LaunchPlan make_launch_plan(const Plan& p);
 std::vector<LGroup> merge_ens_groups(const std::vector<LGroup>& in);
 
 // ---------------------------------------------------- resident program
+constexpr int64_t kLdsBytes = 163840;            // of a CU (gfx950)
 // Tables of k_resident (make_resident): a small model's step for one workgroup
 // per batch column.  Row places are floats of LDS; place 0 holds 1.0.
 constexpr int32_t kResD = 2, kResDec = 2;        // input dimensions, decoded outputs of an ensemble

@@ -1,5 +1,5 @@
 // JSON export of a plan: base arrays, signal placement and the merged groups in
-// execution order with their lowered operands.  Used by tests to compare the
+// execution order with their lowered operands, and the drivers' own programs.  Used by tests to compare the
 // planner bit for bit with an independent implementation.
 #include <sstream>
 
@@ -143,6 +143,16 @@ std::string plan_to_json(const Plan& p) {
   o << ",\"probe_offsets\":";
   jarr(o, p.probe_row_offset);
   o << ",\"feed_rows\":" << ir.feed_rows;
+  // the resident program in the order of the launch drivers' sums and in the
+  // persistent kernel's (a simulator picks one): whether the model has it
+  for (const bool launch : {true, false}) {
+    const ResProgram r = make_resident(p, p.opts.minibatch, kLdsBytes, launch);
+    o << (launch ? ",\"resident\":{\"launch_order\":" : ",\"persistent_order\":") << "{\"ok\":" << (r.ok ? "true" : "false")
+      << ",\"why\":";
+    jstr(o, r.why);
+    o << ",\"slots\":" << r.slots << ",\"waves\":" << r.waves << ",\"lds\":" << r.lds << '}';
+  }
+  o << '}';
   const WindowPlan w = make_window_plan(p);
   o << ",\"window\":{\"ok\":" << (w.ok ? "true" : "false") << ",\"why\":";
   jstr(o, w.why);
@@ -155,6 +165,8 @@ std::string plan_to_json(const Plan& p) {
     jarr(o, pv);
     o << ",\"probe_rows\":";
     jarr(o, w.probe_rows);
+    // `run`: what fuse_window makes of the phase (skip: others do its work)
+    const std::vector<WRun> run = fuse_window(p, w);
     o << ",\"phases\":[";
     for (size_t k = 0; k < w.phases.size(); ++k) {
       if (k) o << ',';
@@ -162,7 +174,8 @@ std::string plan_to_json(const Plan& p) {
         << ",\"a_blk\":" << w.phases[k].a_blk << ",\"exclusive\":" << (w.phases[k].exclusive ? "true" : "false")
         << ",\"group\":";
       jgroup(o, p, w.phases[k].g);
-      o << '}';
+      o << ",\"run\":{\"skip\":" << (run[k].skip ? "true" : "false") << ",\"init\":" << run[k].init
+        << ",\"current\":" << (run[k].jx.base < 0 ? 0 : run[k].fy.base < 0 ? 1 : 2) << "}}";
     }
     o << ']';
   }

@@ -172,6 +172,7 @@ struct ms_sim {
   int64_t scratch_n = 0;             // per-column scratch floats of the persistent kernel
   float* col_scratch = nullptr;      // global scratch when state is not LDS-resident
   bool resident = false;             // the step runs as a resident program (k_resident)
+  std::string res_why;               // why not, where one was tried
   bool res_first = false;            // the next step starts from voltages that a caller set
   ResArgs res{};
   bool res_plain = false;
@@ -1741,6 +1742,12 @@ static void log_sim(const ms_sim* s) {
                dn[s->driver], s->B, p.ir.sigs.size(), p.ir.ops.size(), p.groups.size(),
                (size_t)std::count_if(ls.begin(), ls.end(), [s](const Launch& l) { return launched(s, l); }),
                win ? "window" : "step", (long long)state_b, (long long)param_b);
+  if (s->resident) {   // (the groups below are what its tables were compiled from)
+    std::fprintf(stderr, "mergesim: resident program: %d wavefronts of %d slots, %zu bytes of LDS\n", s->res.waves,
+                 s->res_slots, s->res_lds);
+  } else if (!s->res_why.empty()) {
+    std::fprintf(stderr, "mergesim: no resident program: %s\n", s->res_why.c_str());
+  }
   for (size_t k = 0; k < ls.size(); ++k) {
     const Launch& l = ls[k];
     if (!launched(s, l)) continue;
@@ -1815,6 +1822,7 @@ ms_status ms_sim_create(const ms_model* model, const ms_sim_opts* opts, ms_sim**
       }
       (void)scratch_on(s->device);   // the static staging array's address on this device
       setup_device(s);
+      s->res_why = res.why;
       if (s->driver == MS_DRIVER_PERSISTENT && res.ok) setup_resident(s, res, lds_max);
       else if (s->driver == MS_DRIVER_PERSISTENT) setup_persistent(s);
       if (s->driver == MS_DRIVER_WINDOW) setup_window(s);

@@ -6,7 +6,8 @@ without it, so every probe and the carried voltages equal that driver's bit
 for bit: the launch drivers for models of more than 8,192 rows and fewer than
 eight batch columns, the interpreting persistent kernel otherwise.  A model
 with one unconnected rate ensemble more has no resident program; requested on
-the persistent driver it is that reference.  Sizes: ensembles around the 64
+the persistent driver it is that reference (test_resident_plan checks on the CPU
+that each model here has a program and each reference none).  Sizes: ensembles around the 64
 lanes of a wavefront, of one and two dimensions, with one and several chunks;
 fed rows fewer and more than a workgroup's threads; products of 63 to 128
 columns and rows that are no multiple of eight; runs in pieces."""
@@ -71,19 +72,25 @@ def same(got, ref):
         np.testing.assert_array_equal(a, b)
 
 
-@pytest.mark.parametrize("ns,d,n_feed,K,minibatch", [
+PERSISTENT_ORDER = [
     ((1,), 1, 1, 3, 1), ((63, 64), 1, 3, 5, 2), ((65, 128, 129), 1, 2, 63, 3), ((100,) * 9, 1, 40, 64, 1),
-    ((64,) * 33, 2, 130, 70, 2), ((200, 30), 2, 4, 9, 9), ((60,) * 40, 1, 6, 90, 8)])
+    ((64,) * 33, 2, 130, 70, 2), ((200, 30), 2, 4, 9, 9), ((60,) * 40, 1, 6, 90, 8)]
+
+
+@pytest.mark.parametrize("ns,d,n_feed,K,minibatch", PERSISTENT_ORDER)
 def test_order_of_the_persistent_kernel(ns, d, n_feed, K, minibatch):
     got = run(recurrent(ns, d, minibatch, n_feed, K), [40], 4, driver=M.DRIVER_PERSISTENT)
     same(got, run(recurrent(ns, d, minibatch, n_feed, K, rate=True), [40], 4, driver=M.DRIVER_PERSISTENT))
 
 
-@pytest.mark.parametrize("ns,fill,d,n_feed,K,minibatch", [
+LAUNCH_ORDER = [
     ((64, 1, 63), 90, 1, 5, 64, 1), ((65, 256), 100, 1, 300, 70, 4), ((65, 64), 300, 1, 7, 128, 2), ((64,), 310, 1, 7, 120, 1),
     ((130, 200), 85, 2, 30, 127, 3), ((50,), 90, 2, 600, 63, 5),
     # two decoded sums over up to four chunks, exchanged between lanes, at every place in a block of eight slots
-    ((256, 193, 255, 129, 256), 75, 2, 3, 64, 2)])
+    ((256, 193, 255, 129, 256), 75, 2, 3, 64, 2)]
+
+
+@pytest.mark.parametrize("ns,fill,d,n_feed,K,minibatch", LAUNCH_ORDER)
 def test_order_of_the_launch_drivers(ns, fill, d, n_feed, K, minibatch):
     w = recurrent(ns, d, minibatch, n_feed, K, fill=fill)
     same(run(w, [1, 2, 37], 3), run(w, [40], 3, driver=M.DRIVER_STEPS))
@@ -99,12 +106,42 @@ def test_voltage_above_threshold_then_resident_again():
          run(recurrent(ns, 1, 2, 3, 5, rate=True), [40], 4, state=V, driver=M.DRIVER_PERSISTENT))
 
 
-@pytest.mark.parametrize("ns,fill,d,minibatch", [((64,), 90, 1, 1), ((130, 200), 85, 2, 3), ((65, 256), 100, 1, 4), ((64,), 310, 1, 2)])
+ANY_VOLTAGE = [((64,), 90, 1, 7, 64, 1), ((130, 200), 85, 2, 7, 64, 3), ((65, 256), 100, 1, 7, 64, 4),
+               ((64,), 310, 1, 7, 64, 2)]
+
+
+@pytest.mark.parametrize("ns,fill,d,n_feed,K,minibatch", ANY_VOLTAGE)
 @pytest.mark.parametrize("splits", [[1, 39], [40]])
-def test_any_voltage_in_the_launch_drivers_order(ns, fill, d, minibatch, splits):
+def test_any_voltage_in_the_launch_drivers_order(ns, fill, d, n_feed, K, minibatch, splits):
     """Voltages that a caller set, far above threshold, infinite and negative
     ones among them, in models that would run on the launch drivers."""
-    w = recurrent(ns, d, minibatch, 7, 64, fill=fill)
+    w = recurrent(ns, d, minibatch, n_feed, K, fill=fill)
     V = np.random.default_rng(1).uniform(-1.0, 3.0, (minibatch, ns[0])).astype(np.float32)
     V[0, :6] = np.inf, -np.inf, 1e30, 1.0, np.nextafter(np.float32(1), np.float32(2)), 40.0
     same(run(w, splits, 3, state=V), run(w, splits, 3, state=V, driver=M.DRIVER_STEPS))
+
+
+OPTIONS = [dict(planner_depth=1), dict(planner=MS.PLANNER_GREEDY), dict(sort=False), dict(simplify=False),
+           dict(merge=False)]
+
+
+def option_model(fill, rate=False):
+    return recurrent((65, 64), 1, 2, 3, 5, rate=rate, fill=fill)
+
+
+@pytest.mark.parametrize("opts", OPTIONS)
+def test_plan_options(opts):
+    w = option_model(0)
+    same(run(w, [40], 4, driver=M.DRIVER_PERSISTENT, **opts),
+         run(option_model(0, rate=True), [40], 4, driver=M.DRIVER_PERSISTENT, **opts))
+    w = option_model(90)
+    same(run(w, [3, 37], 3, **opts), run(w, [40], 3, driver=M.DRIVER_STEPS, **opts))
+
+
+def test_the_program_is_what_runs(monkeypatch, capfd):
+    monkeypatch.setenv("MS_LOG", "1")
+    for w, word in ((option_model(0), "mergesim: resident program"), (option_model(90), "mergesim: resident program"),
+                    (option_model(0, rate=True), "mergesim: no resident program: rate neurons")):
+        with M.Simulator(M.model_from_spec(w.spec), minibatch=w.minibatch) as sim:
+            assert sim.info()["driver"] == M.DRIVER_PERSISTENT
+        assert word in capfd.readouterr().err

@@ -79,9 +79,12 @@ def check(w, scalars=True, ensembles=True, driver=None, auto=False, **opts):
         np.testing.assert_array_equal(a, b)
 
 
-@pytest.mark.parametrize("ns,fill,d,n_feed,K,minibatch", [
-    ((65, 64), 0, 1, 3, 70, 2), ((200, 30), 0, 2, 4, 9, 9),            # the persistent kernel's order
-    ((65, 256), 100, 1, 300, 70, 4), ((130, 200), 85, 2, 30, 33, 3)])  # the launch drivers' order
+RESIDENT = [
+    ((65, 64), 0, 1, 3, 70, 2), ((200, 30), 0, 2, 4, 9, 9),           # the persistent kernel's order
+    ((65, 256), 100, 1, 300, 70, 4), ((130, 200), 85, 2, 30, 33, 3)]  # the launch drivers' order
+
+
+@pytest.mark.parametrize("ns,fill,d,n_feed,K,minibatch", RESIDENT)
 def test_resident_program(ns, fill, d, n_feed, K, minibatch):
     check(recurrent(ns, d, minibatch, n_feed, K, fill=fill), driver=M.DRIVER_PERSISTENT, auto=True)
 

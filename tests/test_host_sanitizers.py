@@ -1,5 +1,6 @@
 """The host part of the library (builder, decoder solves, IR, planner, sort,
-window and step programs, JSON export, the model and plan calls) built with
+window and step programs, the window driver's fused phases and the resident
+program, which the JSON export compiles, the model and plan calls) built with
 AddressSanitizer and UndefinedBehaviorSanitizer and driven through the same C
 ABI on every workload shape, every planner option set and the error paths: an
 out-of-bounds access, a use after free or undefined behaviour aborts the run.
@@ -51,6 +52,18 @@ for kind in ("mlp", "chain", "cconv"):
                       {"n_ens": 3, "n_neurons": 20, "dims": 3, "n_eval": 40} if kind == "chain" else
                       {"D": 4, "n_neurons": 10, "n_eval": 40}))
     MS.Plan(MS.model_from_spec(w.spec), minibatch=2, fuse=False, simplify=False).json()
+    n += 1
+# resident programs of every kind of entry, and window phases with dropped copies
+from tests.test_gpu_resident import LAUNCH_ORDER, PERSISTENT_ORDER, recurrent
+from tests.test_launch_plan_mixed_inputs import passthrough_model
+for ns, fill, d, n_feed, K, B in [(a, 0, *b) for a, *b in PERSISTENT_ORDER] + LAUNCH_ORDER:
+    w = recurrent(ns, d, B, n_feed, K, fill=fill)
+    j = MS.Plan(MS.model_from_spec(w.spec), minibatch=B, planner=MS.PLANNER_GREEDY).json()
+    assert j["resident"]["launch_order" if fill else "persistent_order"]["ok"], j["resident"]
+    n += 1
+for o in OPTS:
+    w = passthrough_model(2)
+    assert any(p["run"]["skip"] for p in MS.Plan(MS.model_from_spec(w.spec), minibatch=2, **o).json()["window"]["phases"])
     n += 1
 # error paths: a cycle without synapse, bad ids and shapes, a failing decoder solve
 m = MS.Model()
