@@ -5,8 +5,11 @@ padded to whole tiles) add every sum over k in order into one accumulator, as
 the time-major driver's one-thread-per-row products do, so rate-neuron layers
 fed by them must agree with that driver bit for bit.  Sizes: rows and inputs
 one below, at and one above a tile or slice edge; minibatches with and without
-16-byte aligned columns; few and many column tiles (3840 columns on 256 CUs put
-the large shape on 128 x 128 tiles)."""
+16-byte aligned columns; few and many column tiles.  On 256 CUs the large shapes
+run on 128 x 128 tiles: with aligned columns, and without them 279 tiles (the
+last columns on 64 x 64 tiles), 256 (none left over) and 1144 (past four a CU,
+where the last columns stay on large tiles); none of them whole multiples of a
+tile or slice in every direction."""
 import numpy as np
 import pytest
 
@@ -18,6 +21,7 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = [(n_in, hidden, batch, 6) for n_in in (15, 16, 31, 33) for hidden in (63, 65) for batch in (5, 8)]
 SHAPES += [(129, 128, 7, 9), (130, 129, 12, 11), (257, 193, 12, 5), (1000, 64, 5, 3), (144, 1100, 12, 320)]
+SHAPES += [(145, 1100, 13, 300), (145, 1024, 7, 585), (145, 1300, 13, 1024)]
 
 
 @pytest.mark.parametrize("n_in,hidden,batch,steps", SHAPES)
