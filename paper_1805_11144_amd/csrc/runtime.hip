@@ -207,7 +207,6 @@ struct ms_sim {
   size_t pes_part_n = 0, pes_part_cap = 0;
   // training (window driver)
   bool train_ready = false;
-  bool pack_stale = false;           // weights changed since the forward products' packed weights were made
   std::vector<TrainStep> tsteps;     // backward order
   std::vector<int32_t> trained;      // trained parameter signals
   float* ga = nullptr;               // adjoints, laid out like va
@@ -1351,6 +1350,14 @@ void pack_weights(ms_sim* s, const Launch& l) {
                      (int32_t)kt, l.tr, l.wp);
 }
 
+// The packed weights of the products that read `base` (null: of all), made again
+// where the weights change and not in the next run, which may be the replay of a
+// captured one.
+void repack_weights(ms_sim* s, const float* base) {
+  for (const Launch& l : s->wl)
+    if (l.wp && (!base || l.a_base == base)) pack_weights(s, l);
+}
+
 // Bit-recorded spike probes: their rows leave the float record (the rows of the
 // other probes keep their places in probe_buf) and their bits go to bits_buf,
 // each probe padded to whole 32-neuron words.
@@ -1626,11 +1633,6 @@ void timed_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t 
 void run_window(ms_sim* s, int64_t n_steps) {
   const WindowPlan& w = *s->wplan;
   ensure_window(s, n_steps);
-  if (s->pack_stale) {
-    for (const Launch& l : s->wl)
-      if (l.wp) pack_weights(s, l);
-    s->pack_stale = false;
-  }
   for (int64_t t0 = 0; t0 < n_steps; t0 += s->W) {
     const int32_t T = (int32_t)std::min<int64_t>(s->W, n_steps - t0);
     // phases of one level are independent: spread them over the side streams

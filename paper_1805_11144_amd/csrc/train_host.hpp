@@ -412,8 +412,8 @@ ms_status ms_sim_train_step(ms_sim* s, int64_t n_steps, const ms_feed* feeds, in
         hipLaunchKernelGGL(k_t_sgd, dim3(grid_for(n)), dim3(kBlock), 0, s->stream, s->base_ptr[sg.base] + off,
                            (const float*)(s->gbase[sg.base] + off), n, (float)learning_rate);
       }
+      repack_weights(s, nullptr);
       time_end(s, s->stream);
-      s->pack_stale = true;
     }
     HIPCHECK(hipGetLastError());
     HIPCHECK(hipEventRecord(s->ev1, s->stream));
@@ -469,7 +469,8 @@ ms_status ms_sim_set_train_param(ms_sim* s, int32_t which, int32_t id, int32_t f
     }
     HIPCHECK(hipStreamSynchronize(s->stream));
     HIPCHECK(hipMemcpy(t.p, h.data(), (size_t)n * 4, hipMemcpyHostToDevice));
-    s->pack_stale = true;
+    repack_weights(s, s->base_ptr[s->plan->ir.sigs[t.sig].base]);
+    HIPCHECK(hipStreamSynchronize(s->stream));
     // the other copies made at creation: resident tables, transposed encoders
     // and products, neuron-major decoders, bf16 weights
     // (a simulator that can train has none of them)
