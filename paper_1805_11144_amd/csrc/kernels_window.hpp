@@ -1114,18 +1114,26 @@ __global__ void __launch_bounds__(256, 3) k_w_gemm2(WView w, int32_t M, int32_t 
 }
 
 // Products with fewer 128 x 128 tiles than CUs, few rows or a short K: 64 x 64
-// tiles alone, in slices of 32 k (a wavefront has one accumulator tile here, so
-// a slice of 16 would not cover the loads' latency).
-template <bool VEC>
+// tiles alone, in slices of KS k: 32 from K = kGemmDeepK on, 16 below.  A
+// wavefront has one accumulator tile here, so slices of 32 cover the loads'
+// latency better where there are many of them (K = 500, up to 1000 rows and 3200
+// columns: up to 5% faster than 16).  A short K multiplies zeros up to a whole
+// slice, and slices of 32 let four workgroups on a CU where 16 let eight: 200
+// products of 8 x 48 by 48 x 3150 take 55 us in slices of 16 and 77 in slices of
+// 32, 200 of 16 x 16 by 16 x 3200 31 and 50, 1024 x 128 by 128 x 12800 46 and 50.
+// The two are level between K = 200 and 333.
+constexpr int kGemmDeepK = 256;
+
+template <bool VEC, int KS>
 __global__ void __launch_bounds__(256, 4) k_w_gemm(WView w, int32_t M, int32_t K, int32_t ntiles, int32_t nops,
                                                    const float* P, const int32_t* x_row,
                                                    const int32_t* d_row, int xblk, int store) {
-  __shared__ __attribute__((aligned(16))) float As[2 * 32 * 68], Bs[2 * 32 * 68];
+  __shared__ __attribute__((aligned(16))) float As[2 * KS * 68], Bs[2 * KS * 68];
   const TileIdx t = xcd_tile((uint32_t)((M + 63) / 64), ntiles, nops, blockIdx.x);
   if (!t.live) return;
   const float* X = w.va + (int64_t)G(x_row)[t.op] * w.vs + (int64_t)xblk * w.B;
   float* C = w.va + (int64_t)G(d_row)[t.op] * w.vs + w.B;
-  gemm_tile<64, 64, 32, VEC>(w, M, K, P + (int64_t)t.op * packed_elems(M, K), X, C, (int64_t)t.mt * 64,
+  gemm_tile<64, 64, KS, VEC>(w, M, K, P + (int64_t)t.op * packed_elems(M, K), X, C, (int64_t)t.mt * 64,
                              (int64_t)t.nt * 64, store, As, Bs);
 }
 

@@ -1569,7 +1569,9 @@ void launch_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t
                              dim3(256), 0, q, w, l.M, l.K, (int32_t)mtiles, (int32_t)nbig, (int32_t)l.rows,
                              (const float*)l.wp, l.x_row, l.d_row, l.src_blk, (uint32_t)gbig, l.init.mode);
         } else {
-          hipLaunchKernelGGL(vec ? k_w_gemm<true> : k_w_gemm<false>, dim3((unsigned)(8 * ((mt64 * nt64 * l.rows + 7) / 8))),
+          const auto k64 = l.K < kGemmDeepK ? (vec ? k_w_gemm<true, 16> : k_w_gemm<false, 16>)
+                                     : (vec ? k_w_gemm<true, 32> : k_w_gemm<false, 32>);
+          hipLaunchKernelGGL(k64, dim3((unsigned)(8 * ((mt64 * nt64 * l.rows + 7) / 8))),
                              dim3(256), 0, q, w, l.M, l.K, (int32_t)nt64, (int32_t)l.rows, (const float*)l.wp, l.x_row,
                              l.d_row, l.src_blk, l.init.mode);
         }
