@@ -143,16 +143,6 @@ std::string plan_to_json(const Plan& p) {
   o << ",\"probe_offsets\":";
   jarr(o, p.probe_row_offset);
   o << ",\"feed_rows\":" << ir.feed_rows;
-  // the resident program in the order of the launch drivers' sums and in the
-  // persistent kernel's (a simulator picks one): whether the model has it
-  for (const bool launch : {true, false}) {
-    const ResProgram r = make_resident(p, p.opts.minibatch, kLdsBytes, launch);
-    o << (launch ? ",\"resident\":{\"launch_order\":" : ",\"persistent_order\":") << "{\"ok\":" << (r.ok ? "true" : "false")
-      << ",\"why\":";
-    jstr(o, r.why);
-    o << ",\"slots\":" << r.slots << ",\"waves\":" << r.waves << ",\"lds\":" << r.lds << '}';
-  }
-  o << '}';
   const WindowPlan w = make_window_plan(p);
   o << ",\"window\":{\"ok\":" << (w.ok ? "true" : "false") << ",\"why\":";
   jstr(o, w.why);
@@ -180,7 +170,7 @@ std::string plan_to_json(const Plan& p) {
     o << ']';
   }
   o << '}';
-  // the time-major step program of the launch drivers
+  // the time-major step programs: of the launch drivers, and the resident one
   const LaunchPlan lp = make_launch_plan(p);
   o << ",\"launch\":{\"why\":";
   jstr(o, lp.why);
@@ -192,7 +182,16 @@ std::string plan_to_json(const Plan& p) {
   o << "],\"prologue\":";
   if (lp.has_prologue) jgroup(o, p, lp.prologue);
   else o << "null";
-  o << "}}";
+  // the resident program in the order of the launch drivers' sums and in the
+  // persistent kernel's (a simulator picks one): whether the model has it
+  for (const bool launch : {true, false}) {
+    const ResProgram r = make_resident(p, p.opts.minibatch, kLdsBytes, launch);
+    o << (launch ? ",\"resident\":{\"launch_order\":" : ",\"persistent_order\":") << "{\"ok\":" << (r.ok ? "true" : "false")
+      << ",\"why\":";
+    jstr(o, r.why);
+    o << ",\"slots\":" << r.slots << ",\"waves\":" << r.waves << ",\"lds\":" << r.lds << '}';
+  }
+  o << "}}}";
   return o.str();
 }
 

@@ -59,7 +59,7 @@ from tests.test_launch_plan_mixed_inputs import passthrough_model
 for ns, fill, d, n_feed, K, B in [(a, 0, *b) for a, *b in PERSISTENT_ORDER] + LAUNCH_ORDER:
     w = recurrent(ns, d, B, n_feed, K, fill=fill)
     j = MS.Plan(MS.model_from_spec(w.spec), minibatch=B, planner=MS.PLANNER_GREEDY).json()
-    assert j["resident"]["launch_order" if fill else "persistent_order"]["ok"], j["resident"]
+    assert j["launch"]["resident"]["launch_order" if fill else "persistent_order"]["ok"], j["launch"]["resident"]
     n += 1
 for o in OPTS:
     w = passthrough_model(2)

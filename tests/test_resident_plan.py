@@ -15,7 +15,7 @@ from tests.test_gpu_set_params import RESIDENT as SET_PARAMS
 
 
 def resident(w, **opts):
-    return M.Plan(M.model_from_spec(w.spec), minibatch=w.minibatch, **opts).json()["resident"]
+    return M.Plan(M.model_from_spec(w.spec), minibatch=w.minibatch, **opts).json()["launch"]["resident"]
 
 
 @pytest.mark.parametrize("ns,d,n_feed,K,minibatch", gpu.PERSISTENT_ORDER)
@@ -66,7 +66,7 @@ def ring(E, n=50, d=1, n_feed=1, tau_rc=(0.02,), dt=0.001, K=0, neuron="lif", mi
         spec.connect(Connection(pre=b, post=("ens", ids[0]), transform=0.1, pre_slice=(0, d), synapse=0.01))
     spec.probe(Probe(target=("ens", ids[0]), synapse=0.01))
     return M.Plan(M.model_from_spec(spec), minibatch=minibatch, planner=M.mergesim.PLANNER_GREEDY,
-                  dt=dt).json()["resident"]
+                  dt=dt).json()["launch"]["resident"]
 
 
 # (inside the limit, past it, a word of the reason, order)
