@@ -371,6 +371,7 @@ struct ResProgram {
   std::string why;
   int32_t d = 1, ndec = 1, slots = 0, waves = 1, split_sums = 0, multi = 0, spikes = 0;   // multi: an ensemble takes several slots
   int32_t probe_barrier = 0;                      // spikes: some outputs are stored
+  int32_t ensembles = 0, chunks = 0;
   float tau_rc = 0, tau_ref = 0, amp = 0;
   int64_t lds = 0;                                // bytes
   std::vector<int32_t> row_of;                    // per place: state row (-1: a constant)
@@ -388,6 +389,8 @@ struct ResProgram {
 // are now (null: as planned); the tables' sizes do not depend on their values.
 ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph_order,
                          const std::vector<std::vector<float>>* params = nullptr);
+// Whether a program in the launch drivers' order is faster than those drivers.
+bool resident_beats_launches(const Plan& p, int32_t B, const ResProgram& r);
 
 std::unique_ptr<Plan> make_plan(const Model& m, double dt, const PlanOpts& o);
 std::string plan_to_json(const Plan& p);

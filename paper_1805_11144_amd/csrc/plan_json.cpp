@@ -189,7 +189,9 @@ std::string plan_to_json(const Plan& p) {
     o << (launch ? ",\"resident\":{\"launch_order\":" : ",\"persistent_order\":") << "{\"ok\":" << (r.ok ? "true" : "false")
       << ",\"why\":";
     jstr(o, r.why);
-    o << ",\"slots\":" << r.slots << ",\"waves\":" << r.waves << ",\"lds\":" << r.lds << '}';
+    o << ",\"slots\":" << r.slots << ",\"waves\":" << r.waves << ",\"lds\":" << r.lds;
+    if (launch && r.ok) o << ",\"faster\":" << (resident_beats_launches(p, p.opts.minibatch, r) ? "true" : "false");
+    o << '}';
   }
   o << "}}}";
   return o.str();

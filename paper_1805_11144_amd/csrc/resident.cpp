@@ -256,6 +256,7 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
         for (int32_t n : g.ens_n) {
           if (graph_order && n > 256) return no("an ensemble of more than 256 neurons");
           slots += (n + 63) / 64;
+          ++R.ensembles;
         }
         break;
       }
@@ -272,6 +273,7 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
   // ensembles have theirs)
   if (slots > (int64_t)kResWaves * (R.d == 1 ? kResSlots[2] : kResSlots[1])) return no("more neurons than the wavefronts' registers hold");
   R.tau_rc = first->tau_rc[0]; R.tau_ref = first->tau_ref[0]; R.amp = first->amp[0];
+  R.chunks = (int32_t)slots;
   R.waves = (int32_t)std::min<int64_t>(kResWaves, std::max<int64_t>(1, (slots + 3) / 4));   // about four slots each
   if (ir.feed_rows > 2 * 64 * R.waves) return no("more feed rows than the workgroup fetches ahead");
   std::vector<Item> G;
@@ -550,6 +552,28 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
   if ((int64_t)R.weights.size() > (1 << 20)) return no("products too large for one workgroup");
   R.ok = true;
   return R;
+}
+
+// A step of the launch drivers takes about 2.2 us a launch and 2 us more, so the
+// program is the faster one past three launches: 5 of them take 11.7 to 16.8 us, the
+// same models 4.5 to 9.6 with it.  Two or three (one fused ensemble launch, one
+// of synapses, the feed's) use the whole chip for 7.2 or 10.4 us, about 2 more
+// where the ensembles' workgroups no longer fit at once (1024 of 256 threads).
+// The program's step grows with the chunks a wavefront holds, by the form of its
+// neurons, and with its items.  Of 388 models of two or three launches measured
+// on both (80 to 320 chunks, 1 to 7 columns, 1 to 16 connections an ensemble),
+// those this lets through are up to twice as fast and one is slower, by 3%
+// (8.08, 7.87 us); a ring of 320 ensembles of 50 neurons takes 7.7 us with the
+// program and 7.3 as launches, 80 of 250 9.7 and 7.1, 160 of 50 5.3 and 7.1.
+bool resident_beats_launches(const Plan& p, int32_t B, const ResProgram& r) {
+  const size_t launches = make_launch_plan(p).step.size();
+  if (launches > 3) return true;
+  const double per_wave = (r.chunks + r.waves - 1) / r.waves;
+  const double neurons = r.d == 2 ? 4.8 + per_wave * (r.spikes ? 0.09 : 0.055)
+                         : r.spikes ? 3.7 + per_wave * 0.19
+                                    : 2.5 + per_wave * (r.multi ? 0.17 : 0.12);
+  return neurons + 0.0005 * (double)(r.items.size() + r.entries.size() / 2) <=
+         (launches == 3 ? 10.4 : 7.2) + ((int64_t)r.ensembles * B > 1024 ? 2.2 : 0.0);
 }
 
 }  // namespace ms

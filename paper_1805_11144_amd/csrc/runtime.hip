@@ -1003,15 +1003,20 @@ bool small_model(const Plan& p, int32_t B) {
 // `res` receives the resident program when the persistent driver is chosen and
 // the model has one.  A recurrent model that is not small in the sense above ran
 // on the launch drivers before there was a resident form; with one it is
-// faster as well: 320 ensembles of 50 neurons in 14 groups, minibatch 1,
-// 15.9 instead of 32 us a step.  (The kernel takes at most 320 chunks of 64
-// neurons, so larger models stay on the launch drivers.)
+// faster as well, 320 ensembles of 50 neurons in 14 groups, minibatch 1, 15.9
+// instead of 32 us a step, unless its step is a few launches and it has many
+// neurons (resident_beats_launches).  The kernel takes at most 320 chunks of 64
+// neurons, so larger models stay on the launch drivers.
 int32_t choose_driver(const Plan& p, int32_t B, int32_t requested, int64_t lds_bytes, ResProgram& res) {
   if (requested != MS_DRIVER_AUTO && requested != MS_DRIVER_PERSISTENT) return requested;
   if (has_learning(p)) return requested == MS_DRIVER_AUTO ? MS_DRIVER_GRAPH : requested;
   if (requested == MS_DRIVER_AUTO && make_window_plan(p).ok) return MS_DRIVER_WINDOW;
   const bool persistent = requested == MS_DRIVER_PERSISTENT || small_model(p, B);
   res = make_resident(p, B, lds_bytes, !persistent);
+  if (!persistent && res.ok && !resident_beats_launches(p, B, res)) {
+    res = ResProgram{};
+    res.why = "the launch drivers are faster";
+  }
   return persistent || res.ok ? MS_DRIVER_PERSISTENT : MS_DRIVER_GRAPH;
 }
 

@@ -46,7 +46,7 @@ def test_plan_options(opts):
     assert r["launch_order"]["ok"], r
 
 
-def ring(E, n=50, d=1, n_feed=1, tau_rc=(0.02,), dt=0.001, K=0, neuron="lif", minibatch=1):
+def ring_spec(E, n=50, d=1, n_feed=1, tau_rc=(0.02,), dt=0.001, K=0, neuron="lif", spikes=False):
     """E ensembles in a ring, the first one fed; K: a K x K product over them."""
     rng = np.random.default_rng(E)
     spec = ModelSpec(dt=dt)
@@ -65,7 +65,13 @@ def ring(E, n=50, d=1, n_feed=1, tau_rc=(0.02,), dt=0.001, K=0, neuron="lif", mi
         spec.connect(Connection(pre=a, post=b, transform=rng.standard_normal((K, K))))
         spec.connect(Connection(pre=b, post=("ens", ids[0]), transform=0.1, pre_slice=(0, d), synapse=0.01))
     spec.probe(Probe(target=("ens", ids[0]), synapse=0.01))
-    return M.Plan(M.model_from_spec(spec), minibatch=minibatch, planner=M.mergesim.PLANNER_GREEDY,
+    if spikes:
+        spec.probe(Probe(target=("neurons", ids[0])))
+    return spec
+
+
+def ring(E, minibatch=1, dt=0.001, planner=M.mergesim.PLANNER_GREEDY, **kw):
+    return M.Plan(M.model_from_spec(ring_spec(E, dt=dt, **kw)), minibatch=minibatch, planner=planner,
                   dt=dt).json()["launch"]["resident"]
 
 
@@ -93,3 +99,19 @@ def test_limits(inside, past, why, order):
     assert r["ok"], r
     r = ring(**past)[order]
     assert not r["ok"] and why in r["why"], r
+
+
+# (model, minibatch, whether the program was measured faster than the launch drivers)
+CHOICE = [
+    # a ring's step is two launches
+    (dict(E=160), 1, True), (dict(E=320), 1, False), (dict(E=320), 4, True), (dict(E=80, n=250), 1, False),
+    (dict(E=80, n=250), 7, False), (dict(E=20, n=250), 1, True), (dict(E=128, d=2), 1, True),
+    (dict(E=240, spikes=True), 1, False), (dict(E=160, spikes=True), 7, True),
+    # twelve with a product
+    (dict(E=300, K=64), 1, True), (dict(E=80, n=250, K=64), 4, True)]
+
+
+@pytest.mark.parametrize("model,minibatch,faster", CHOICE)
+def test_choice_against_the_launch_drivers(model, minibatch, faster):
+    r = ring(**model, minibatch=minibatch, planner=M.mergesim.PLANNER_TREE)["launch_order"]
+    assert r["ok"] and r["faster"] == faster, r
