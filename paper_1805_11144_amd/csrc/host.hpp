@@ -5,7 +5,9 @@
 #pragma once
 
 #include <cstdint>
+#include <algorithm>
 #include <array>
+#include <iterator>
 #include <map>
 #include <memory>
 #include <stdexcept>
@@ -299,6 +301,32 @@ struct WindowPlan {
 };
 
 WindowPlan make_window_plan(const Plan& p);
+
+// The phases (merged groups) that write or read a row, in order.  There are a few
+// for each of thousands of rows, so up to three are held without an allocation.
+struct Phases {
+  int32_t n = 0, in[3];
+  std::vector<int32_t> more;   // all of them when there are more than three
+  const int32_t* begin() const { return n <= 3 ? in : more.data(); }
+  const int32_t* end() const { return begin() + n; }
+  size_t size() const { return (size_t)n; }
+  int32_t operator[](size_t k) const { return begin()[k]; }
+  bool ends_with(int32_t k) const { return n > 0 && begin()[n - 1] == k; }
+  void push_back(int32_t k) {
+    if (n < 3) in[n] = k;
+    else if (n == 3) more.assign(in, in + 3);
+    if (n >= 3) more.push_back(k);
+    ++n;
+  }
+  // Those of `o` join, k leaves; `both`: room to work in.
+  void take(const Phases& o, int32_t k, std::vector<int32_t>& both) {
+    both.clear();
+    std::set_union(begin(), end(), o.begin(), o.end(), std::back_inserter(both));
+    n = 0;
+    for (int32_t q : both)
+      if (q != k) push_back(q);
+  }
+};
 
 // How the window driver runs one phase (fuse_window): the phase's group with
 // its operand rows, and what it took over from others.

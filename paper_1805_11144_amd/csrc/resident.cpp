@@ -33,7 +33,7 @@ struct Prep {
   std::vector<Item>& G;
   int64_t nrows;
   std::vector<char> probed;
-  std::vector<std::vector<int32_t>> writers, readers;
+  std::vector<Phases> writers, readers;   // per row
 
   bool batched(const LOperand& o) const { return o.base >= 0 && p.ir.bases[o.base].cls == SC_BATCHED; }
 
@@ -65,12 +65,14 @@ struct Prep {
     }
   }
   void index() {
-    writers.assign((size_t)nrows, {});
-    readers.assign((size_t)nrows, {});
+    writers.resize((size_t)nrows);
+    readers.resize((size_t)nrows);
+    for (Phases& v : writers) v.n = 0;
+    for (Phases& v : readers) v.n = 0;
     for (int32_t k = 0; k < (int32_t)G.size(); ++k) {
       if (G[k].skip) continue;
-      each_write(G[k].g, [&](int64_t r) { if (writers[r].empty() || writers[r].back() != k) writers[r].push_back(k); });
-      each_read(G[k].g, [&](int64_t r) { if (readers[r].empty() || readers[r].back() != k) readers[r].push_back(k); });
+      each_write(G[k].g, [&](int64_t r) { if (!writers[r].ends_with(k)) writers[r].push_back(k); });
+      each_read(G[k].g, [&](int64_t r) { if (!readers[r].ends_with(k)) readers[r].push_back(k); });
     }
   }
 
@@ -89,7 +91,7 @@ struct Prep {
       std::vector<int64_t> rows;
       std::vector<float> vals;
       each_write(it.g, [&](int64_t r) {
-        const std::vector<int32_t>& w = writers[r];
+        const Phases& w = writers[r];
         if (!ok || w.size() < 2 || w[1] != k || G[w[0]].g.type != OP_RESET || (from >= 0 && w[0] != from)) { ok = false; return; }
         from = w[0];
         for (int32_t q : readers[r]) if (q > from && q < k) ok = false;   // would see the reset value
@@ -146,21 +148,26 @@ struct Prep {
   // Copies of whole rows whose readers, later in the step, find the source
   // unchanged: they read it instead.
   void drop_copies() {
+    std::vector<int32_t> alias((size_t)nrows, -1), both;
     for (int32_t k = 0; k < (int32_t)G.size(); ++k) {
       const LGroup& g = G[k].g;
       if (G[k].skip || !batched(g.src)) continue;
       if (!(g.type == OP_COPY || (g.type == OP_COPY_INC && G[k].init && G[k].vals.empty() && entries(g) == g.rows))) continue;
-      std::vector<int32_t> alias((size_t)nrows, -1), rd;
+      std::vector<int32_t> rd;
       bool ok = true;
       for (int64_t r = 0; r < g.rows && ok; ++r) {
         const int64_t d = row_at(g.dst, r), s = row_at(g.src, r);
         ok = writers[d].size() == 1 && !probed[d];
-        alias[d] = (int32_t)s;
         for (int32_t q : readers[d]) {
           if (q <= k) ok = false;   // reads the previous step's value
           for (int32_t wk : writers[s]) if (wk > k && wk <= q) ok = false;
-          rd.push_back(q);
         }
+      }
+      if (!ok) continue;
+      for (int64_t r = 0; r < g.rows; ++r) {
+        const int64_t d = row_at(g.dst, r);
+        alias[d] = (int32_t)row_at(g.src, r);
+        rd.insert(rd.end(), readers[d].begin(), readers[d].end());
       }
       std::sort(rd.begin(), rd.end());
       rd.erase(std::unique(rd.begin(), rd.end()), rd.end());
@@ -169,12 +176,17 @@ struct Prep {
         saved.push_back(G[rd[i]]);
         ok = rewrite(G[rd[i]].g, alias);
       }
-      if (ok) {
+      if (ok) {   // the sources' readers are now the copies' readers as well, but not group k
         G[k].skip = true;
-        index();
+        for (int64_t r = 0; r < g.rows; ++r) {
+          const int64_t d = row_at(g.dst, r);
+          readers[row_at(g.src, r)].take(readers[d], k, both);
+          readers[d].n = writers[d].n = 0;
+        }
       } else {
         for (size_t i = 0; i < saved.size(); ++i) G[rd[i]] = saved[i];
       }
+      for (int64_t r = 0; r < g.rows; ++r) alias[row_at(g.dst, r)] = -1;
     }
   }
 

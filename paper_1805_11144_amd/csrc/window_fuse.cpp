@@ -14,7 +14,6 @@
 // Each row's value is formed by the same operations in the same order, so the
 // results are the same (a copied -0 may become +0 and back).
 #include <algorithm>
-#include <iterator>
 
 #include "host.hpp"
 
@@ -35,28 +34,6 @@ LOperand operand_of(int32_t base, std::vector<int32_t> rows) {
 }
 
 int64_t entries(const LGroup& g) { return g.ptr.empty() ? g.rows : (int64_t)g.ptr.back(); }
-
-// The phases that write or read a row, in order.  There are a few for each of
-// thousands of rows, so up to three are held without an allocation.
-struct Phases {
-  int32_t n = 0, in[3];
-  std::vector<int32_t> more;   // all of them when there are more than three
-  const int32_t* begin() const { return n <= 3 ? in : more.data(); }
-  const int32_t* end() const { return begin() + n; }
-  size_t size() const { return (size_t)n; }
-  int32_t operator[](size_t k) const { return begin()[k]; }
-  bool ends_with(int32_t k) const { return n > 0 && begin()[n - 1] == k; }
-  void push_back(int32_t k) {
-    if (n < 3) in[n] = k;
-    else if (n == 3) more.assign(in, in + 3);
-    if (n >= 3) more.push_back(k);
-    ++n;
-  }
-  void assign(const std::vector<int32_t>& v) {
-    n = 0;
-    for (int32_t k : v) push_back(k);
-  }
-};
 
 struct Fuser {
   const Plan& p;
@@ -301,11 +278,7 @@ struct Fuser {
         std::vector<int32_t> both;
         for (int64_t r = 0; r < g.rows; ++r) {
           const int64_t d = row_at(g.dst, r);
-          Phases& s = readers[row_at(g.src, r)];
-          both.clear();
-          std::set_union(s.begin(), s.end(), readers[d].begin(), readers[d].end(), std::back_inserter(both));
-          both.erase(std::remove(both.begin(), both.end(), k), both.end());
-          s.assign(both);
+          readers[row_at(g.src, r)].take(readers[d], k, both);
           readers[d].n = writers[d].n = 0;
         }
       } else {
