@@ -1207,16 +1207,22 @@ __global__ void k_probe_extract(const float* buf, int32_t B, int64_t T, int32_t 
   out[_i] = buf[(t * probe_rows + off + j) * B + b];
 }
 
-// The same for B >= kExtractB, as a transposition through LDS: the output is
-// [B][q] with q = t w + j, so a workgroup takes 64 values of q and 64 batch
-// columns, reads each q as a row segment along B and writes each column as a
-// segment along q.  Bound by the copy (one read, one write of the record); one
-// thread per output element reads B floats apart instead, a cache line for
-// each value: a record of 1024 values, 256 columns and 50 steps takes 65 us,
-// here 39 us.
-// Below kExtractB columns a line still serves several lanes of the simple form
-// and a 64-wide tile would be mostly empty.  Grid (ceil(T w / 64), ceil(B / 64)).
+// The same as a transposition through LDS: the output is [B][q] with q = t w + j,
+// so a workgroup takes 64 values of q and 64 batch columns, reads each q as a row
+// segment along B and writes each column as a segment along q.  One thread per
+// output element reads B floats apart instead, a cache line for each value, which
+// is the slower form once the record leaves the L2s: a record of 1024 values, 256
+// columns and 50 steps takes 65 us, here 39 (2.7 TB/s: segments of 256 bytes at a
+// stride on both sides stay below the 4.8 of a plain copy).
+// Smaller records are served by the L2s there, and here a wavefront's sixteen
+// loads and a barrier stand in a row.  A whole read, here / there in us: 64
+// columns 17 / 13 with 0.1 M values, 17 / 17 with 1 M, 18 / 23 with 1.5 M, 27 / 85
+// with 6 M, and the same from 32 to 4096 columns; 16 columns 20 / 15 with 1 M, 26
+// / 20 with 2 M, 28 / 34 with 2.5 M.  Below 16 columns a line serves several lanes
+// there and most of a tile is empty here (8 columns: 47 / 28 with 3.2 M).
+// Grid (ceil(T w / 64), ceil(B / 64)).
 constexpr int kExtractB = 16;
+constexpr int64_t kExtractN = 9 << 17;   // values of a record; twice that below 32 columns
 
 __global__ void __launch_bounds__(256) k_probe_extract_t(const float* buf, int32_t B, int64_t T, int32_t probe_rows,
                                                          int32_t off, int32_t w, float* out) {

@@ -1994,7 +1994,8 @@ static void extract_probe(ms_sim* s, int32_t probe, float* out) {
   const Plan& p = *s->plan;
   const int32_t w = p.probe_width[probe];
   const int64_t T = s->steps_total, n = (int64_t)s->B * T * w;
-  if (s->B >= kExtractB && s->B <= 64 * 65535 && T * w <= 64LL * 2147483647)   // within the grid's limits
+  if (s->B >= kExtractB && n >= (s->B < 32 ? 2 : 1) * kExtractN && s->B <= 64 * 65535 &&
+      T * w <= 64LL * 2147483647)   // (the last two: within the grid's limits)
     hipLaunchKernelGGL(k_probe_extract_t, dim3((unsigned)((T * w + 63) / 64), (unsigned)((s->B + 63) / 64)), dim3(256),
                        0, s->stream, (const float*)s->probe_buf, s->B, T, s->probe_rows, p.probe_row_offset[probe], w,
                        out);

@@ -1,9 +1,9 @@
 """GPU: probe records read back in the caller's [batch, steps, width] layout.
 
 A probed input node records its feed unchanged, so every read must equal the
-feed bit for bit.  The batch sizes lie at the edges of the read's two forms (a
-64 x 64 transposition tile from 16 batch columns on, one thread per value
-below), the widths and step counts make (step, value) pairs cross tile
+feed bit for bit.  The batch sizes lie at the edges of the read's two forms (large
+records a 64 x 64 transposition tile from 16 batch columns on, others one thread
+per value), the widths and step counts make (step, value) pairs cross tile
 boundaries, and two probes put the second one at an offset in the record."""
 import numpy as np
 import pytest
@@ -13,6 +13,17 @@ import paper_1805_11144_amd as M
 from synth.spec import ModelSpec, Node, Probe
 
 pytestmark = pytest.mark.gpu
+
+
+# records on the transposition tiles: 1,179,648 values, twice that below 32
+# columns; the first two lie on both sides of the line
+LARGE = [(64, 96, 96), (64, 96, 95), (16, 128, 576), (17, 101, 688), (33, 77, 233), (65, 1, 9085), (130, 130, 36),
+         (1100, 541, 1), (257, 63, 37)]
+
+
+@pytest.mark.parametrize("batch,width,steps", LARGE)
+def test_large_record_is_the_feed(batch, width, steps):
+    test_record_is_the_feed(batch, width, steps)
 
 
 @pytest.mark.parametrize("batch", [1, 15, 16, 63, 65, 130])
