@@ -467,8 +467,8 @@ ms_status ms_sim_set_train_param(ms_sim* s, int32_t which, int32_t id, int32_t f
     } else {
       std::copy(in, in + n, h.begin());
     }
-    HIPCHECK(hipStreamSynchronize(s->stream));
-    HIPCHECK(hipMemcpy(t.p, h.data(), (size_t)n * 4, hipMemcpyHostToDevice));
+    // on the simulator's stream, behind its runs, and with one wait for all
+    HIPCHECK(hipMemcpyAsync(t.p, h.data(), (size_t)n * 4, hipMemcpyHostToDevice, s->stream));
     repack_weights(s, s->base_ptr[s->plan->ir.sigs[t.sig].base]);
     HIPCHECK(hipStreamSynchronize(s->stream));
     // the other copies made at creation: resident tables, transposed encoders
