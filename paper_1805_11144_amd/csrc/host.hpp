@@ -378,7 +378,11 @@ constexpr int64_t kLdsBytes = 163840;            // of a CU (gfx950)
 // per batch column.  Row places are floats of LDS; place 0 holds 1.0.
 constexpr int32_t kResD = 2, kResDec = 2;        // input dimensions, decoded outputs of an ensemble
 constexpr int32_t kResWaves = 8;
-constexpr int32_t kResSlots[] = {4, 16, 40};     // neurons per lane the kernel is compiled for (40: d = ndec = 1)
+// Neurons per lane the kernel is compiled for.  40 (d = ndec = 1) are as many as
+// the registers take, in the blocks of eight whose decoded sums are formed
+// together: at four registers each, 40 leave 96 of 256 to the rest and spill
+// none, or 8 in the form with lookups; 48 spill 36 and 52.
+constexpr int32_t kResSlots[] = {4, 16, 40};
 // Entries of a wavefront's list: {type | kResBar | kResPut, first item, a, b}.
 //   RES_SIMPLE, RES_SUM4, RES_INC, RES_DOT: `a` items from the first one on
 //   RES_ENS: slots a .. b - 1; RES_TREE: b units from unit a on

@@ -5,15 +5,19 @@
 // merged groups of a few rows, and an interpreter that fetches each group's
 // descriptor, indices and parameters from L2 (k_persistent) spends 12,000
 // cycles a step on it, a hipGraph of one launch per group about 2 us a group.
-// Here every neuron's state, encoder and bias stay in registers for the whole
-// run, all other rows, the decoders and the items of work in LDS.  Each wavefront
-// runs its own list of entries, held in its lanes, and fetches the next
-// entry's items while it works on the current one.
+// Here every neuron's state, encoder and bias are loaded into registers once a
+// run (with 40 slots the form with lookups spills 8 of 256 registers, read back
+// from scratch each step), all other rows, the decoders and the items of work are
+// in LDS.  Each wavefront runs its own list of entries, held in its lanes, and
+// fetches the next entry's items while it works on the current one.
 // Every sum is taken in the order of the driver that would otherwise run the
 // model, so the results are the same bits.  Measured a step: one recurrent ensemble of
 // 100 neurons 2.2 us (k_persistent 4.9), 320 ensembles of 50 neurons in 14
-// groups 15.9 us (launches 32), of which the neuron updates, which issue on all
-// four SIMDs of the one CU, are more than half.
+// groups 15.8 us (launches 32).  By shader counters the first is bound by its
+// serial chain: of its one wavefront's 5,160 cycles a step it issues in 51% (340
+// VALU, 180 scalar, 40 LDS instructions) and waits for LDS and barriers in the
+// rest.  The second is bound by VALU issue on the four SIMDs of its CU, busy 65%
+// of the time; its wavefronts wait 42% of theirs.
 //
 // Neurons: lane r of slot s of a wavefront holds neuron r of a 64-neuron chunk of
 // one ensemble; consecutive slots hold an ensemble's chunks.

@@ -1003,7 +1003,7 @@ bool small_model(const Plan& p, int32_t B) {
 // `res` receives the resident program when the persistent driver is chosen and
 // the model has one.  A recurrent model that is not small in the sense above ran
 // on the launch drivers before there was a resident form; with one it is
-// faster as well, 320 ensembles of 50 neurons in 14 groups, minibatch 1, 15.9
+// faster as well, 320 ensembles of 50 neurons in 14 groups, minibatch 1, 15.8
 // instead of 32 us a step, unless its step is a few launches and it has many
 // neurons (resident_beats_launches).  The kernel takes at most 320 chunks of 64
 // neurons, so larger models stay on the launch drivers.
@@ -1558,6 +1558,13 @@ void launch_phase(ms_sim* s, const Launch& l, int32_t T, int64_t t0, hipStream_t
         const int64_t ncu = std::max<int32_t>(1, s->n_cu), per_col = mtiles * l.rows, tiles = ntiles * per_col;
         if (mt64 * nt64 * l.rows >= 2147483648LL - 16) fail(MS_E_INVALID, "window product too large for the GEMM grid");
         if (l.K > 128 && l.M >= 64 && tiles >= ncu) {
+          // Fewer 128 x 128 tiles than CUs leave some idle: 1024 x 1024 by 1024 x
+          // 3072 (192 of them) takes 112 us on them and 85 on 64 x 64 tiles.  The
+          // two are level at 288 (129, 127) and from 320 on the large ones lead by
+          // up to 8%, where M fills them (512 rows and more); at K = 144 they are
+          // level at 600 and above.  What this line still gets wrong: 256 to 288
+          // tiles (114, 104 at 256), and ops of at most 320 rows, on which the small
+          // tiles are up to twice as fast.
           // 128 x 128 tiles in XCD order, padded to a multiple of 8; column
           // tiles beyond the last whole multiple of the CUs as 64 x 64 tiles
           // (past 4 tiles a CU the remainder is under a fifth of the launch)
