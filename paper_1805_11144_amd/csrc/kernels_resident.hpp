@@ -38,14 +38,11 @@ typedef int res_i4 __attribute__((ext_vector_type(4)));
 
 // neuron_update for spiking neurons with dt <= tau_rc / 16: the same values by
 // the same operations, selected instead of branched to, so that several neurons'
-// updates overlap.  The partial step's exponent is at least -1/16, and from V <=
-// 1 the overshoot ratio q is below 1 - exp(-1/16) < 1/16, so the polynomial
-// branches are the ones taken.  (Only where V is within an ulp of 1 and J within
-// a few of it can rounding leave a larger q, up to 0.12: the polynomial's
-// truncation q^7 / 8 is then still below an ulp, but the last bit may differ
-// from log1pf's.)  FIRST: for a step from voltages that a caller set, which may
-// be above 1; after it every voltage is at most 1.
-template <bool FIRST>
+// updates overlap.  The partial step's exponent is at least -1/16, so expm1's
+// polynomial is the branch taken.  An overshoot ratio q above 1/16 (voltages that
+// a caller set above threshold, or V and J within a few ulp of 1) crosses before
+// the step began: tau_rc (-ln(1 - q)), tau_rc times the polynomial (no less than
+// q) and the q >= 1 case all end at `integ`, which is at most tau_rc / 16.
 __device__ __forceinline__ float res_neuron(float j, float& v, float& rf, const ResArgs& A, float amp_dt, float dt) {
   const float integ = __builtin_amdgcn_fmed3f(dt - rf, 0.0f, dt);
   const float ep = expm1_small(-integ * A.inv_tau);
@@ -54,8 +51,7 @@ __device__ __forceinline__ float res_neuron(float j, float& v, float& rf, const 
   float rn = __builtin_amdgcn_fmed3f(rf - dt, 0.0f, __builtin_inff());
   const float drive = j - 1.0f;
   const float q = (vn - 1.0f) * __builtin_amdgcn_rcpf(drive);
-  const float crossed = A.tau_rc * (!FIRST || q <= 0.0625f ? neg_log1m_small(q) : -log1pf(-q));
-  const float since = FIRST && q >= 1.0f ? integ : fminf(crossed, integ);
+  const float since = fminf(A.tau_rc * neg_log1m_small(q), integ);
   float rs = A.tau_ref - (drive > 0.0f ? since : 0.0f);
   __asm__ volatile("" : "+v"(rn), "+v"(rs));   // computed on every lane (see lif_update_bf)
   const bool spk = vn > 1.0f;
@@ -127,8 +123,8 @@ __device__ __forceinline__ float res_tree8(const float (&p)[8], int lane) {
 
 // PLAIN: every ensemble has at most 64 neurons and stores its decoded output
 // only.  Without that, a slot's place in its ensemble and its spikes' place are
-// looked up.  FIRST: see res_neuron.
-template <int D, int ND, int S, bool PLAIN, bool FIRST = false>
+// looked up.
+template <int D, int ND, int S, bool PLAIN>
 __global__ void __launch_bounds__(512) k_resident(float* state, int64_t rows, int32_t B, ResArgs A, int64_t n_steps,
                                                   float dt, const float* stage, int32_t feed_rows, float* probe_buf,
                                                   int64_t t0) {
@@ -249,7 +245,7 @@ __global__ void __launch_bounds__(512) k_resident(float* state, int64_t rows, in
 #pragma unroll
           for (int q = 0; q < D; ++q) j += enc[s][q] * x[u][q];
           float v = V[s], rf = R[s];
-          sp[u] = res_neuron<FIRST>(j, v, rf, A, amp_dt, dt);
+          sp[u] = res_neuron(j, v, rf, A, amp_dt, dt);
           const bool in = s >= lo && s < hi;   // slots of other ensemble groups keep their state
           V[s] = in ? v : V[s];
           R[s] = in ? rf : R[s];

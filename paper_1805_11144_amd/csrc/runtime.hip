@@ -173,7 +173,6 @@ struct ms_sim {
   float* col_scratch = nullptr;      // global scratch when state is not LDS-resident
   bool resident = false;             // the step runs as a resident program (k_resident)
   std::string res_why;               // why not, where one was tried
-  bool res_first = false;            // the next step starts from voltages that a caller set
   ResArgs res{};
   bool res_plain = false;
   int32_t res_d = 1, res_slots = 0;
@@ -1052,14 +1051,8 @@ struct Uploads {
   }
 };
 
-// first: for the step after a caller set voltages (one form for plain models too)
-const void* resident_kernel(const ms_sim* s, bool first) {
+const void* resident_kernel(const ms_sim* s) {
   const int S = s->res_slots;
-  if (first && s->res_d > 1)
-    return S == 4 ? (const void*)k_resident<2, 2, 4, false, true> : (const void*)k_resident<2, 2, 16, false, true>;
-  if (first)
-    return S == 4 ? (const void*)k_resident<1, 1, 4, false, true>
-           : S == 16 ? (const void*)k_resident<1, 1, 16, false, true> : (const void*)k_resident<1, 1, 40, false, true>;
   if (s->res_d > 1) return S == 4 ? (const void*)k_resident<2, 2, 4, false> : (const void*)k_resident<2, 2, 16, false>;
   if (s->res_plain)
     return S == 4 ? (const void*)k_resident<1, 1, 4, true>
@@ -1122,29 +1115,16 @@ void setup_resident(ms_sim* s, const ResProgram& R, int lds_max) {
   s->resident = true;
   // the device's limit, not this model's size: simulators share the kernel
   if (s->res_lds > 65536)
-    for (const bool first : {false, true})
-      HIPCHECK(hipFuncSetAttribute(resident_kernel(s, first), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
+    HIPCHECK(hipFuncSetAttribute(resident_kernel(s), hipFuncAttributeMaxDynamicSharedMemorySize, lds_max));
 }
 
-// The step after a caller set voltages is a launch of its own, whose neuron
-// update takes any voltage.  So is the first step of a run that the caller
-// captures: voltages may be set between the replays.
 void run_resident(ms_sim* s, int64_t n_steps) {
   int64_t rows = (int64_t)std::max<size_t>(1, s->state_rows);
   int32_t fr = s->plan->ir.feed_rows;
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  HIPCHECK(hipStreamIsCapturing(s->stream, &cap));
-  auto launch = [&](bool first, int64_t k0, int64_t n) {
-    const float* stage = s->feed_stage + k0 * fr * s->B;
-    int64_t t0 = s->steps_total + k0;
-    void* args[] = {&s->state, &rows, &s->B, &s->res, &n, &s->dt, &stage, &fr, &s->probe_buf, &t0};
-    HIPCHECK(hipLaunchKernel(resident_kernel(s, first), dim3((unsigned)s->B), dim3((unsigned)(64 * s->res.waves)), args,
-                             s->res_lds, s->stream));
-  };
-  const int64_t k = s->res_first || cap != hipStreamCaptureStatusNone ? 1 : 0;
-  if (k) launch(true, 0, 1);
-  if (n_steps > k) launch(false, k, n_steps - k);
-  s->res_first = false;
+  const float* stage = s->feed_stage;
+  void* args[] = {&s->state, &rows, &s->B, &s->res, &n_steps, &s->dt, &stage, &fr, &s->probe_buf, &s->steps_total};
+  HIPCHECK(hipLaunchKernel(resident_kernel(s), dim3((unsigned)s->B), dim3((unsigned)(64 * s->res.waves)), args,
+                           s->res_lds, s->stream));
 }
 
 void setup_persistent(ms_sim* s) {
@@ -2100,7 +2080,6 @@ static void reset_state(ms_sim* s) {
   if (launch_driver(s)) HIPCHECK(hipMemsetAsync(s->ctr, 0, 2 * sizeof(int64_t), s->stream));
   init_state(s);
   s->steps_total = 0;
-  s->res_first = false;
 }
 
 ms_status ms_sim_reset(ms_sim* s) {
@@ -2195,8 +2174,6 @@ ms_status ms_sim_set_state(ms_sim* s, int32_t which, int32_t id, const float* in
     const int32_t sig = state_signal(s, which, id);
     if (n_elems != (int64_t)s->plan->ir.sigs[sig].rows * s->B) fail(MS_E_INVALID, "state size mismatch");
     state_copy(s, sig, const_cast<float*>(in), true);
-    if (which == MS_STATE_VOLTAGE)   // k_resident's usual neuron update starts from V <= 1
-      for (int64_t k = 0; k < n_elems; ++k) s->res_first |= in[k] > 1.0f;
   });
 }
 

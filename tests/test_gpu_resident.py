@@ -97,8 +97,8 @@ def test_order_of_the_launch_drivers(ns, fill, d, n_feed, K, minibatch):
 
 
 def test_voltage_above_threshold_then_resident_again():
-    """A voltage above threshold, which only a caller can set, takes one step of
-    the form whose neuron update handles it."""
+    """Voltages above threshold, which only a caller can set, in the order of the
+    persistent kernel."""
     ns = (65, 64)
     V = np.random.default_rng(0).uniform(0.5, 1.5, (2, 65)).astype(np.float32)
     a = recurrent(ns, 1, 2, 3, 5)

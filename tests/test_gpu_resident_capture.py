@@ -34,3 +34,26 @@ def test_voltages_set_between_replays_of_a_captured_run():
             torch.cuda.synchronize()
             for p in range(4):
                 np.testing.assert_array_equal(sim.data(p), eager.data(p)[:, k * n:])
+
+
+def test_voltages_set_before_a_capture():
+    """A run captured but not replayed leaves the voltages to the next eager run."""
+    w = recurrent((65, 64), 1, 2, 3, 5)
+    n, model = 10, M.model_from_spec(w.spec)
+    feeds = {i: torch.from_numpy(np.ascontiguousarray(f[:, :n])).cuda() for i, f in w.feeds.items()}
+    V = np.random.default_rng(2).uniform(0.5, 2.5, (2, 65)).astype(np.float32)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with M.Simulator(model, minibatch=2, probe_capacity_steps=64, driver=M.DRIVER_PERSISTENT) as eager, \
+            M.Simulator(model, minibatch=2, probe_capacity_steps=64, driver=M.DRIVER_PERSISTENT,
+                        stream=stream.cuda_stream) as sim:
+        for s in (eager, sim):
+            s.set_state(MS.STATE_VOLTAGE, 0, V)
+        with torch.cuda.graph(torch.cuda.CUDAGraph(), stream=stream):
+            sim.run_steps(n, feeds)
+        eager.run_steps(n, feeds)
+        sim.run_steps(n, feeds)
+        for k in (MS.STATE_VOLTAGE, MS.STATE_REFRACTORY):
+            np.testing.assert_array_equal(sim.get_state(k, 0, 65), eager.get_state(k, 0, 65))
+        for p in range(4):
+            np.testing.assert_array_equal(sim.data(p)[:, n:], eager.data(p))
