@@ -334,6 +334,33 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
     for (int64_t q = 1; q < n; ++q) if (at(row + q) != at(row) + q) return false;
     return true;
   };
+  // k_persistent takes a product's sums in parts
+  auto parts_of = [&](const LGroup& g) {
+    const int64_t out = g.rows * (int64_t)g.M, threads = nrows <= 4096 ? 256 : 1024;
+    int32_t parts = 1;
+    while (!graph_order && parts < 64 && out * parts * 2 <= threads && parts * 2 <= g.K) parts *= 2;
+    return parts;
+  };
+  auto tree_sums = [&](const LGroup& g) { return graph_order && g.K >= 64 && B <= 4; };
+  // ---- wavefronts: also about two entries of the level with the most rows and
+  // products (16 columns of a product count as one more), or of the probes.  By
+  // the neurons alone one ensemble of 50 neurons had one wavefront: beside a
+  // product of 500 x 500 a step took 279 us (k_persistent 99), with eight 38.
+  std::vector<double> busy((size_t)nlev, 0.0);
+  for (size_t k = 0; k < G.size(); ++k) {
+    if (G[k].skip || G[k].g.type == OP_ENS) continue;
+    const LGroup& g = G[k].g;
+    double e = (double)g.rows / 64;
+    if (g.type == OP_DOT_INC && tree_sums(g)) {
+      e = (double)g.rows * ((g.M + 7) / 8);
+    } else if (g.type == OP_DOT_INC) {
+      const int32_t parts = parts_of(g);
+      e *= (double)g.M * parts * (1.0 + (double)((g.K + parts - 1) / parts) / 16);
+    }
+    busy[(size_t)level[k]] += e;
+  }
+  const double most_busy = std::max(*std::max_element(busy.begin(), busy.end()), (double)p.probe_src_rows.size() / 64);
+  R.waves = std::max(R.waves, (int32_t)std::min<double>(kResWaves, std::ceil(most_busy / 2)));
   // ---- tables
   struct Slot { int32_t x = 0, d = 0, s = -1, n = 0, flags = 0, V = 0, ref = 0; std::vector<float> enc, bias, dec; };
   std::vector<std::vector<Slot>> ws((size_t)R.waves);
@@ -421,7 +448,7 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
           const std::vector<float>& W = param(g.a.base);
           for (int64_t o = 0; o < g.rows; ++o)
             if (!together(g.x_row[o], g.K) || !together(g.d_row[o], g.M)) return no("a product whose rows are apart");
-          if (graph_order && g.K >= 64 && B <= 4) {   // rows of W across the lanes
+          if (tree_sums(g)) {   // rows of W across the lanes
             for (int64_t o = 0; o < g.rows; ++o)
               for (int32_t m = 0; m < g.M; m += 8) {
                 const int32_t n = std::min(8, g.M - m);
@@ -432,10 +459,7 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
               }
             break;
           }
-          // a row per lane, W transposed; k_persistent takes the sum in parts
-          int32_t parts = 1;
-          const int64_t out = g.rows * (int64_t)g.M, threads = nrows <= 4096 ? 256 : 1024;
-          while (!graph_order && parts < 64 && out * parts * 2 <= threads && parts * 2 <= g.K) parts *= 2;
+          const int32_t parts = parts_of(g);   // a row per lane, W transposed
           for (int64_t o = 0; o < g.rows; ++o) {
             const int32_t off = (int32_t)R.weights.size();
             for (int32_t q = 0; q < g.K; ++q)
@@ -562,6 +586,20 @@ ResProgram make_resident(const Plan& p, int32_t B, int64_t lds_bytes, bool graph
           (int64_t)R.units.size() * 4 + nslot * 32 + (int64_t)R.slot_dec.size() * 4 + (int64_t)R.entries.size() * 4;
   if (R.lds > lds_bytes) return no("rows and tables past the LDS");
   if ((int64_t)R.weights.size() > (1 << 20)) return no("products too large for one workgroup");
+  // k_persistent runs models of more than 4096 rows on 1024 threads, which take
+  // large products better than 512, while its ensembles are the slower ones: with
+  // 300 x 300 weights 30 ensembles of 100 neurons take 25.8 us a step on it, 27.3
+  // here, 300 of 64 50.3 and 33.9; with 500 x 500 the 30 take 36 and 48, with 500 x
+  // 100 0.88 times as long here.  Smaller models run on 256 threads there, and
+  // several columns share a CU, where 16 slots' registers let one column alone have
+  // it: with 300 columns 4 ensembles of 400 neurons and 500 x 100 weights 35 and
+  // 46, with 100 x 100 level, with 64 columns half as long here.
+  int64_t nweight = 0;
+  for (const LGroup& g : p.lowered)
+    if (g.type == OP_DOT_INC) nweight += g.rows * (int64_t)g.M * g.K;
+  if (!graph_order && (nrows > 4096 ? nweight > 48 * 1024 + 300 * (int64_t)R.chunks
+                                    : B > 256 && R.slots > kResSlots[0] && nweight > 8192))
+    return no("products that k_persistent runs faster");
   R.ok = true;
   return R;
 }

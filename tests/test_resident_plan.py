@@ -90,6 +90,9 @@ LIMITS = [
     (dict(E=2, K=128), dict(E=2, K=129), "long product", "launch_order"),
     (dict(E=2, K=129), dict(E=2, K=1025), "one workgroup", "persistent_order"),
     (dict(E=2, minibatch=7), dict(E=2, minibatch=8), "one workgroup", "launch_order"),
+    (dict(E=60, n=64, K=250), dict(E=60, n=64, K=300), "k_persistent", "persistent_order"),   # 66 k weights
+    (dict(E=12, n=150, K=90, minibatch=300), dict(E=12, n=150, K=91, minibatch=300), "k_persistent", "persistent_order"),
+    (dict(E=12, n=150, K=91, minibatch=256), dict(E=12, n=150, K=91, minibatch=257), "k_persistent", "persistent_order"),
 ]
 
 
@@ -115,3 +118,10 @@ CHOICE = [
 def test_choice_against_the_launch_drivers(model, minibatch, faster):
     r = ring(**model, minibatch=minibatch, planner=M.mergesim.PLANNER_TREE)["launch_order"]
     assert r["ok"] and r["faster"] == faster, r
+
+
+@pytest.mark.parametrize("model,waves", [
+    (dict(E=1), 1), (dict(E=4), 1), (dict(E=5), 2), (dict(E=40), 8),                       # four chunks a wavefront
+    (dict(E=1, K=40), 3), (dict(E=1, K=200), 8), (dict(E=1, n_feed=128), 2)])              # rows, columns of a product
+def test_wavefronts(model, waves):
+    assert ring(**model)["persistent_order"]["waves"] == waves
