@@ -206,6 +206,8 @@ struct ms_sim {
   size_t pes_part_n = 0, pes_part_cap = 0;
   // training (window driver)
   bool train_ready = false;
+  std::vector<PackJob> pack_jobs, dx_jobs;   // packed weights of the forward products, of those that carry adjoints
+  PackJob *pack_dev = nullptr, *dx_dev = nullptr;
   std::vector<TrainStep> tsteps;     // backward order
   std::vector<int32_t> trained;      // trained parameter signals
   float* ga = nullptr;               // adjoints, laid out like va
@@ -1327,20 +1329,36 @@ void alloc_packed(ms_sim* s, Launch& l) {
   s->extra_allocs.push_back(l.wp);
 }
 
-// (Re)packs a launch's weights as they are now.
-void pack_weights(ms_sim* s, const Launch& l) {
-  const int64_t mt = (l.M + 63) / 64, kt = (l.K + kGemmPadK - 1) / kGemmPadK, n = l.rows * mt * kt;
-  if (n > 2147483647LL) fail(MS_E_INVALID, "product too large for the packed weights' grid");
-  hipLaunchKernelGGL(k_w_pack, dim3((unsigned)n), dim3(256), 0, s->stream, l.a_base, l.w_row, l.M, l.K, (int32_t)mt,
-                     (int32_t)kt, l.tr, l.wp);
+int64_t pack_blocks(const PackJob& j) { return (int64_t)j.nops * j.mtiles * j.ktiles; }
+
+void add_pack_job(std::vector<PackJob>& jobs, const Launch& l) {
+  const int64_t mt = (l.M + 63) / 64, kt = (l.K + kGemmPadK - 1) / kGemmPadK;
+  const int64_t first = jobs.empty() ? 0 : jobs.back().first + pack_blocks(jobs.back());
+  if (l.rows * mt * kt > 2147483647LL) fail(MS_E_INVALID, "product too large for the packed weights' grid");
+  PackJob j{l.a_base, l.w_row, l.wp, l.M, l.K, (int32_t)mt, (int32_t)kt, l.tr, (int32_t)l.rows, first};
+  jobs.push_back(j);
+}
+
+// Packs the weights of jobs lo .. hi - 1 (dev: their copy on the device) as they
+// are now, in launches of at most the grid's 2^24 - 1 workgroups of 256.
+void pack_weights(ms_sim* s, const std::vector<PackJob>& jobs, const PackJob* dev, size_t lo, size_t hi) {
+  while (lo < hi) {
+    size_t q = lo;
+    int64_t n = 0;
+    do n += pack_blocks(jobs[q++]);
+    while (q < hi && n + pack_blocks(jobs[q]) < (1 << 24));
+    hipLaunchKernelGGL(k_w_pack, dim3((unsigned)n), dim3(256), 0, s->stream, dev + lo, (int32_t)(q - lo));
+    lo = q;
+  }
 }
 
 // The packed weights of the products that read `base` (null: of all), made again
 // where the weights change and not in the next run, which may be the replay of a
 // captured one.
 void repack_weights(ms_sim* s, const float* base) {
-  for (const Launch& l : s->wl)
-    if (l.wp && (!base || l.a_base == base)) pack_weights(s, l);
+  if (!base) return pack_weights(s, s->pack_jobs, s->pack_dev, 0, s->pack_jobs.size());
+  for (size_t k = 0; k < s->pack_jobs.size(); ++k)
+    if (s->pack_jobs[k].W == base) pack_weights(s, s->pack_jobs, s->pack_dev, k, k + 1);
 }
 
 // Bit-recorded spike probes: their rows leave the float record (the rows of the
@@ -1460,8 +1478,10 @@ void setup_window(ms_sim* s) {
     if (!packed(l)) continue;
     l.wp = wp;
     wp += l.rows * packed_elems(l.M, l.K);
-    pack_weights(s, l);
+    add_pack_job(s->pack_jobs, l);
   }
+  if (!s->pack_jobs.empty()) s->pack_dev = upload(s, s->pack_jobs);
+  repack_weights(s, nullptr);
   if (s->lds_limit > 65536) {
     const void* wens[] = {(const void*)k_w_ens<1, false, false>, (const void*)k_w_ens<2, false, false>,
                           (const void*)k_w_ens<4, false, false>, (const void*)k_w_ens<8, false, false>,

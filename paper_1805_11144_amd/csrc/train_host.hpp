@@ -182,7 +182,10 @@ void setup_train(ms_sim* s) {
             lx.w_row = upload(s, wr);
             lx.x_row = upload(s, xr);
             lx.d_row = upload(s, dr);
-            if (packed) alloc_packed(s, lx);
+            if (packed) {
+              alloc_packed(s, lx);
+              add_pack_job(s->dx_jobs, lx);
+            }
             st.dx_l.push_back(lx);
           }
         }
@@ -193,6 +196,7 @@ void setup_train(ms_sim* s) {
     }
     s->tsteps.push_back(std::move(st));
   }
+  if (!s->dx_jobs.empty()) s->dx_dev = upload(s, s->dx_jobs);
   s->train_ready = true;
 }
 
@@ -214,6 +218,7 @@ void run_backward(ms_sim* s, int32_t T) {
   const WView w{s->va, s->vs, s->B, T};
   const double tb = (double)T * s->B;
   hipStream_t q = s->stream;
+  bool packed = false;
   for (const TrainStep& st : s->tsteps) {
     const Launch& l = s->wl[st.phase];
     switch (st.type) {
@@ -285,10 +290,9 @@ void run_backward(ms_sim* s, int32_t T) {
             hipLaunchKernelGGL(k_t_transpose, dim3(grid_for(n)), dim3(kBlock), 0, q, l.a_base, l.w_row, l.M, l.K, n,
                                st.wt);
           }
-          for (const Launch& lx : st.dx_l) {
-            if (lx.wp) pack_weights(s, lx);
-            launch_phase(s, lx, T, 0, q, s->ga);
-          }
+          if (!packed) pack_weights(s, s->dx_jobs, s->dx_dev, 0, s->dx_jobs.size());   // of every step, with the first one
+          packed = true;
+          for (const Launch& lx : st.dx_l) launch_phase(s, lx, T, 0, q, s->ga);
           time_end(s, q);
         }
         break;

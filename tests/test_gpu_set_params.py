@@ -13,6 +13,7 @@ import pytest
 
 import paper_1805_11144_amd as M
 from synth import make_workload
+from synth.spec import Connection, ModelSpec, Node, Probe
 from tests.test_gpu_resident import recurrent
 
 pytestmark = pytest.mark.gpu
@@ -109,3 +110,31 @@ def test_launch_driver_many_neurons():
 def test_window_products(gemm_dtype):
     w = make_workload("c3", neuron_type="relu", n_steps=10, minibatch=8, n_hidden=72, n_in=24, n_out=3)
     check(w, scalars=False, ensembles=False, driver=M.DRIVER_WINDOW, gemm_dtype=gemm_dtype)   # gains are not set
+
+
+SIZES = [(17, 16), (33, 40), (64, 100), (65, 31), (130, 33), (1, 64)]
+
+
+def test_packed_weights_of_many_products():
+    """Products of six shapes, their weights packed by one launch, and by a launch
+    of its own where one transform is set."""
+    rng, B, steps = np.random.default_rng(3), 5, 4
+    spec = ModelSpec(dt=0.001)
+    u = spec.add_node(Node(size=100))
+    for rows, cols in SIZES:
+        o = spec.add_node(Node(size=rows, passthrough=True))
+        spec.connect(Connection(pre=u, post=o, transform=rng.standard_normal((rows, cols)), pre_slice=(0, cols)))
+        spec.probe(Probe(target=o))
+    feeds = {u[1]: rng.standard_normal((B, steps, 100)).astype(np.float32)}
+    model = M.model_from_spec(spec)
+    with M.Simulator(model, minibatch=B, driver=M.DRIVER_WINDOW) as win, \
+            M.Simulator(model, minibatch=B, driver=M.DRIVER_STEPS) as ref:
+        for k in range(-1, len(SIZES)):
+            for s in (win, ref):
+                if k >= 0:
+                    s.set_train_param(MS.TRAIN_TRANSFORM, k, np.random.default_rng(k).standard_normal(SIZES[k]))
+                s.reset()
+                s.run_steps(steps, feeds)
+            for p in range(len(SIZES)):
+                assert np.abs(ref.data(p)).max() > 0
+                np.testing.assert_array_equal(win.data(p), ref.data(p))
