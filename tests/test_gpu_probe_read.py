@@ -43,6 +43,7 @@ def test_record_is_the_feed(batch, width, steps):
             np.testing.assert_array_equal(sim.data(p), want)
             np.testing.assert_array_equal(sim.data_static(p), want)
             dev = torch.full(want.shape, float("nan"), device="cuda")
+            torch.cuda.synchronize()   # the fill is on torch's stream, the read on the simulator's
             ptr = M.mergesim.C.cast(dev.data_ptr(), M.mergesim._fp)
             assert M.load_library().ms_sim_probe_read(sim.handle, p, ptr, dev.numel(), 1) == 0
             np.testing.assert_array_equal(dev.cpu().numpy(), want)
